@@ -39,14 +39,14 @@ def listed():
         # 2D laser wakefield: density ramp (charge per particle), open y
         _case("laser_2d_f32", "steps", "512x256", "0.1x0.2", 2, 4, 16, 0.0, 20, "po", 20, laser=True),
         # the headline benchmark: 128^3 warm plasma, 8 per cell, quadratic
-        _case("warm_3d_f32", "steps", "128x128x128", "0.2x0.2x0.2", 2, 4, 8, 0.05, 10),
+        _case("warm_3d_f32", "steps", "128x128x128", "0.2x0.2x0.2", 2, 4, 8, 0.05, 20),
         # the same in double precision
-        _case("warm_3d_f64", "steps", "128x128x128", "0.2x0.2x0.2", 2, 8, 8, 0.05, 10),
+        _case("warm_3d_f64", "steps", "128x128x128", "0.2x0.2x0.2", 2, 8, 8, 0.05, 20),
         # 3D laser wakefield, cubic, open y and z: the largest
         _case("laser_3d_f32", "steps", "256x128x128", "0.1x0.2x0.2", 3, 4, 8, 0.0, 12, "poo", 12,
               laser=True),
         # electrons and mobile ions, linear shapes, a mesh that no tile divides
-        _case("ions_3d_f32", "steps", "100x75x50", "0.2x0.2x0.2", 1, 4, 8, 0.05, 10, ions=True),
+        _case("ions_3d_f32", "steps", "100x75x50", "0.2x0.2x0.2", 1, 4, 8, 0.05, 20, ions=True),
         # moving window with a laser antenna and fresh plasma entering in front
         _case("window_3d_f32", "window", "160x48x48", "0.2x0.2x0.2", 2, 4, 8, 0.01, 14, "ooo"),
         # one field advance on a mesh of odd sizes with open faces
