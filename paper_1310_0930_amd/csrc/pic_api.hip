@@ -11,7 +11,6 @@
 #include "pic_internal.h"
 
 namespace pic {
-long mur_len(const pic_config& cf);
 long diag_len(const pic_config& cf);
 long adj_len(const pic_config& cf);
 
@@ -36,9 +35,6 @@ WsLayout ws_layout(const pic_ctx* ctx, int64_t np) {
   off = align256(off + sizeof(int) * (size_t)ctx->ntiles);
   L.rb_nl = off;
   off = align256(off + sizeof(int) * (size_t)ctx->ntiles);
-  L.mur_len = (size_t)mur_len(ctx->cfg);
-  L.mur = off;
-  off = align256(off + R * L.mur_len);
   L.diag_len = (size_t)diag_len(ctx->cfg);
   L.diag = off;
   off = align256(off + sizeof(double) * L.diag_len);
@@ -162,7 +158,6 @@ int pic_create(const pic_config* cfg, pic_ctx** out) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return PIC_EHIP;
-  if (static_scratch_init(dev) != 0) return PIC_EHIP;  // pic_field_advance_static's scratch
   pic_ctx* ctx = new (std::nothrow) pic_ctx();
   if (!ctx) return PIC_EHIP;
   ctx->cfg = *cfg;
@@ -304,17 +299,31 @@ int pic_field_advance(pic_ctx* ctx, pic_fields* f, void* ws, void* stream) {
   int v = check_fields(f, true);
   if (v) return v;
   if ((v = ensure_device(ctx))) return v;
-  return hip_status(launch_field_advance(ctx, f, ws, (hipStream_t)stream));
+  return hip_status(launch_field_advance(ctx, f, (hipStream_t)stream));
 }
+
+// Bytes of the E samples on both open faces of every open axis and next to
+// them, the quantity pic_field_advance_static's contract limits.
+static size_t face_bytes(const pic_config& c) {
+  size_t len = 0;
+  for (int d = 0; d < c.dims; ++d) {
+    if (c.bc[d] != PIC_BC_OPEN) continue;
+    size_t face = 1;
+    for (int e = 0; e < c.dims; ++e)
+      if (e != d) face *= (size_t)c.n[e];
+    len += 4 * face;
+  }
+  return len * (size_t)c.real_bytes;
+}
+constexpr size_t STATIC_FACE_BYTES = (size_t)16 << 20;
 
 int pic_field_advance_static(pic_ctx* ctx, pic_fields* f, void* stream) {
   if (!ctx) return PIC_EINVAL;
   int v = check_fields(f, true);
   if (v) return v;
-  if ((size_t)mur_len(ctx->cfg) * (size_t)ctx->cfg.real_bytes > STATIC_SCRATCH_BYTES)
-    return PIC_ESCRATCH;
+  if (face_bytes(ctx->cfg) > STATIC_FACE_BYTES) return PIC_ESCRATCH;
   if ((v = ensure_device(ctx))) return v;
-  return hip_status(launch_field_advance_static(ctx, f, (hipStream_t)stream));
+  return hip_status(launch_field_advance(ctx, f, (hipStream_t)stream));
 }
 
 int pic_step(pic_ctx* ctx, pic_particles* p, pic_fields* f, int32_t nsteps, void* ws, void* stream) {
@@ -577,7 +586,7 @@ const char* pic_strerror(int status) {
     case PIC_ESTATE: return "call order violated (sort the particles first)";
     case PIC_EDEVICE: return "device flags raised";
     case PIC_ELDS: return "tile geometry exceeds the LDS of a compute unit";
-    case PIC_ESCRATCH: return "grid needs more scratch than the static no-allocation buffer holds";
+    case PIC_ESCRATCH: return "open faces too large for the workspace-free field advance";
     default: return "unknown status";
   }
 }
