@@ -115,7 +115,8 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   static constexpr bool fits = S > 0;
   static constexpr int TZ = fits ? B::TZ / S : 1;
   static constexpr int ez = DIMS == 3 ? TZ + 2 * B::AZ + Rc::g_hi - Rc::g_lo : 1;
-  static constexpr int e_vol = B::ex * B::ex * ez;
+  static constexpr int es = B::ex, ep = B::ex * B::ex;
+  static constexpr int e_vol = ep * ez, e_cnt = e_vol;
   static constexpr int jz = DIMS == 3 ? TZ + 2 * B::AZ + Rc::d_hi - Rc::d_lo : 1;
   static constexpr int j_vol = B::jx * B::jx * jz;
 };

@@ -119,16 +119,16 @@ struct LdsFields {
     // stencil read is a small immediate from it (paired LDS reads reach 255
     // elements; left to itself the compiler folds the array and component
     // offsets into the immediates and then needs an address add per pair)
-    return pin(s + comp * G::e_vol + base + (b[2] * G::ex + b[1]) * G::ex + b[0]);
+    return pin(s + comp * G::e_vol + base + b[2] * G::ep + b[1] * G::es + b[0]);
   }
   // planes 0 and 1 of the stencil are within reach of the first node's
   // register; planes 2 and 3 get a second register (far)
   __device__ __forceinline__ lds_ptr<const R> far(lds_ptr<const R> r) const {
-    return DIMS == 3 && ORDER >= 2 ? pin(r + 2 * G::ex * G::ex) : r;
+    return DIMS == 3 && ORDER >= 2 ? pin(r + 2 * G::ep) : r;
   }
   __device__ __forceinline__ lds_ptr<const R> plane(lds_ptr<const R> r, lds_ptr<const R> r2,
                                                     int k) const {
-    return k < 2 ? r + k * G::ex * G::ex : r2 + (k - 2) * G::ex * G::ex;
+    return k < 2 ? r + k * G::ep : r2 + (k - 2) * G::ep;
   }
   // One LDS read per value: paired reads (ds_read2) of neighbouring samples
   // cost gfx950's LDS about twice the cycles of two single reads for the
@@ -138,7 +138,7 @@ struct LdsFields {
   // them.
   __device__ __forceinline__ R at(lds_ptr<const R> rk, int /*comp*/, int i, int j, int /*k*/) const {
     using vptr = __attribute__((address_space(3))) const volatile R*;
-    return ((vptr)rk)[j * G::ex + i];
+    return ((vptr)rk)[j * G::es + i];
   }
   static __device__ __forceinline__ lds_ptr<const R> pin(lds_ptr<const R> p) {
     uint32_t a = (uint32_t)(uintptr_t)p;
@@ -192,13 +192,13 @@ struct LdsCurrent {
   int base;  // the particle's old cell in the J region
   double* seg;
   __device__ __forceinline__ void segment(const int* b) {
-    seg = s + base + (b[2] * G::jx + b[1]) * G::jx + b[0];
+    seg = s + base + b[2] * G::jc + b[1] * G::jb + b[0] * G::ja;
   }
   // arithmetic type of the contributions: double for the fixed-point tile
   using C = typename std::conditional<G::fixed, double, R>::type;
   // add the contribution f * a
   __device__ __forceinline__ void put(int comp, int i, int j, int k, C f, C a) const {
-    double* t = &seg[comp * G::j_vol + (k * G::jx + j) * G::jx + i];
+    double* t = &seg[comp * G::j_vol + k * G::jc + j * G::jb + i * G::ja];
     if constexpr (G::fixed) {
       // |f a| < 2^51: adding 1.5 * 2^52 rounds the product to an integer n
       // held in the low mantissa bits (one rounding, fused); the bit pattern
@@ -697,7 +697,7 @@ __device__ inline void stage_load(const KParams<R>& P, const DFields<R>& F, cons
       const int r = tid + k * G::NT;
 #pragma unroll
       for (int c = 0; c < 6; ++c) stage[k][c] = R(0);
-      if (r < G::e_vol) {
+      if (r < G::e_cnt) {
         const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
         const int o = base + (DIMS == 3 ? lz * str2 : 0) + ly * str1 + lx;
 #pragma unroll
@@ -711,7 +711,7 @@ __device__ inline void stage_load(const KParams<R>& P, const DFields<R>& F, cons
     const int r = tid + k * G::NT;
 #pragma unroll
     for (int c = 0; c < 6; ++c) stage[k][c] = R(0);
-    if (r < G::e_vol) {
+    if (r < G::e_cnt) {
       const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
       int sx[2], sy[2], sz[2] = {0, 0};
       axis_slots(org[0] + G::e_lo + lx, P.n[0], open0, 1, sx);

@@ -52,10 +52,11 @@ struct CrossQueue {
   // o1 and q back from the particle arrays, where the main loop stored them
   // (the 3D current has no q v_z term)
   static constexpr size_t compact_rec = 2 * sizeof(int) + DIMS * sizeof(R);
-  static constexpr int full_cap = 96 * NW;
-  static constexpr bool compact = DIMS == 3 && full_cap * full_rec > room;
+  // 64 to 96 full records per wavefront if they fit
+  static constexpr bool compact = DIMS == 3 && 64 * NW * full_rec > room;
+  static constexpr int full_cap = 96 * NW * full_rec <= room ? 96 * NW : (int)(room / full_rec);
   static constexpr int CAP = compact ? (int)(room / compact_rec) : full_cap;
-  static constexpr bool on = compact ? CAP >= 64 : full_cap * full_rec <= room;
+  static constexpr bool on = compact ? CAP >= 64 : CAP >= 64 * NW;
   static constexpr int LEN = on ? CAP : 1;
   static constexpr int LENV = on && !compact ? CAP : 1;  // full records only
   static constexpr int LENI = on && compact ? CAP : 1;   // compact records only
@@ -221,7 +222,7 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
   if (tile < 0) return;
   int pbeg = __builtin_amdgcn_readfirstlane(s_q[0][1]);
   int pend = __builtin_amdgcn_readfirstlane(s_q[0][2]);
-  constexpr int NR = (G::e_vol + G::NT - 1) / G::NT;
+  constexpr int NR = (G::e_cnt + G::NT - 1) / G::NT;
   R stage[NR][6];
   int org[3];
   tile_origin<DIMS, ORDER, R>(P, tile, org);
@@ -234,9 +235,11 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int r = tid + k * G::NT;
-      if (r < G::e_vol) {
+      if (r < G::e_cnt) {
+        const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
+        const int e = lz * G::ep + ly * G::es + lx;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) s_eb[c * G::e_vol + r] = stage[k][c];
+        for (int c = 0; c < 6; ++c) s_eb[c * G::e_vol + e] = stage[k][c];
       }
     }
   };
@@ -380,7 +383,8 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
       }
       if (valid) {
         LdsFields<DIMS, ORDER, R> acc{
-            (lds_ptr<const R>)s_eb, ((l[2] - G::e_lo_z) * G::ex + (l[1] - G::e_lo)) * G::ex + (l[0] - G::e_lo)};
+            (lds_ptr<const R>)s_eb,
+            (l[2] - G::e_lo_z) * G::ep + (l[1] - G::e_lo) * G::es + (l[0] - G::e_lo)};
         R Ep[3], Bp[3];
         gather<DIMS, ORDER, R>(acc, s.o, Ep, Bp);
         bool small = false;
@@ -395,7 +399,8 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
           valid = false;
         }
       }
-      const int pbase = ((l[2] - G::j_lo_z) * G::jx + (l[1] - G::j_lo)) * G::jx + (l[0] - G::j_lo);
+      const int pbase =
+          (l[2] - G::j_lo_z) * G::jc + (l[1] - G::j_lo) * G::jb + (l[0] - G::j_lo) * G::ja;
       // A path that stays in the same piece of the shape along every axis is
       // one virtual segment from the old to the new offset in that piece's
       // frame, on the stencil of the old cell's piece.
@@ -475,23 +480,25 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     if (axis_inside(jbx, G::jx, P.n[0], open0) && axis_inside(jby, G::jx, P.n[1], open1) &&
         (DIMS == 2 || axis_inside(jbz, G::jz, P.n[2], open2))) {
       const int base = (DIMS == 3 ? jbz * str2 : 0) + jby * str1 + jbx;
-      for (int r = opaque_tid(); r < G::j_vol; r += G::NT) {
+      for (int r = opaque_tid(); r < G::j_cnt; r += G::NT) {
         const int lx = r % G::jx, ly = (r / G::jx) % G::jx, lz = r / (G::jx * G::jx);
+        const int t = lz * G::jc + ly * G::jb + lx * G::ja;
         const int o = base + (DIMS == 3 ? lz * str2 : 0) + ly * str1 + lx;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           R v;
           if constexpr (G::fixed)
-            v = (R)ldexp((double)sext48(((const long long*)s_j)[c * G::j_vol + r]), -Ks[c]);
+            v = (R)ldexp((double)sext48(((const long long*)s_j)[c * G::j_vol + t]), -Ks[c]);
           else
-            v = (R)s_j[c * G::j_vol + r];
-          s_j[c * G::j_vol + r] = 0.0;
+            v = (R)s_j[c * G::j_vol + t];
+          s_j[c * G::j_vol + t] = 0.0;
           if (v != R(0)) atomic_add(&F.J[c][o], v);
         }
       }
     } else {
-      for (int r = opaque_tid(); r < G::j_vol; r += G::NT) {
+      for (int r = opaque_tid(); r < G::j_cnt; r += G::NT) {
         const int lx = r % G::jx, ly = (r / G::jx) % G::jx, lz = r / (G::jx * G::jx);
+        const int t = lz * G::jc + ly * G::jb + lx * G::ja;
         int sx[2], sy[2], sz[2] = {0, 0};
         axis_slots(org[0] + G::j_lo + lx, P.n[0], open0, 1, sx);
         axis_slots(org[1] + G::j_lo + ly, P.n[1], open1, str1, sy);
@@ -500,10 +507,10 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
         for (int c = 0; c < 3; ++c) {  // J_c staggered along c
           R v;
           if constexpr (G::fixed)
-            v = (R)ldexp((double)sext48(((const long long*)s_j)[c * G::j_vol + r]), -Ks[c]);
+            v = (R)ldexp((double)sext48(((const long long*)s_j)[c * G::j_vol + t]), -Ks[c]);
           else
-            v = (R)s_j[c * G::j_vol + r];
-          s_j[c * G::j_vol + r] = 0.0;
+            v = (R)s_j[c * G::j_vol + t];
+          s_j[c * G::j_vol + t] = 0.0;
           const int ix = sx[c == 0], iy = sy[c == 1], iz = sz[c == 2];
           if (v != R(0) && ix >= 0 && iy >= 0 && iz >= 0) atomic_add(&F.J[c][ix + iy + iz], v);
         }

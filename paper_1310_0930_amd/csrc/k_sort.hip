@@ -637,14 +637,13 @@ __global__ void k_fill_int(int* a, long n, int v) {
 // The region whose banks the placement balances: the field region in single
 // precision (the gather's 6 (n+1)^D four-byte reads outweigh the deposit's
 // 8-byte adds), the current region in double (its double adds take twice the
-// LDS cycles of the 64-bit integer adds); the two share their strides at
-// even orders.
+// LDS cycles of the 64-bit integer adds); lanes that are conflict-free in one
+// are so in the other (Geo's strides).
 template <int DIMS, int ORDER, typename R>
 static void region_strides_t(SortParams& S) {
   using G = Geo<DIMS, ORDER, R>;
-  constexpr int rx = sizeof(R) == 4 ? G::ex : G::jx;
-  S.rs1 = rx;
-  S.rs2 = DIMS == 3 ? rx * rx : 0;
+  S.rs1 = sizeof(R) == 4 ? G::es : G::jb;
+  S.rs2 = DIMS == 3 ? (sizeof(R) == 4 ? G::ep : G::jc) : 0;
 }
 
 template <typename R>

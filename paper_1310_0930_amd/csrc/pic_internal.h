@@ -44,13 +44,51 @@ struct Geo {
   static constexpr int ez = DIMS == 3 ? TZ + 2 * AZ + Rc::g_hi - Rc::g_lo : 1;
   static constexpr int e_lo = -A + Rc::g_lo;  // region origin relative to the tile origin
   static constexpr int e_lo_z = DIMS == 3 ? e_lo : 0;
-  static constexpr int e_vol = ex * ex * ez;
   // J region
   static constexpr int jx = T + 2 * A + Rc::d_hi - Rc::d_lo;
   static constexpr int jz = DIMS == 3 ? TZ + 2 * AZ + Rc::d_hi - Rc::d_lo : 1;
   static constexpr int j_lo = -A + Rc::d_lo;
   static constexpr int j_lo_z = DIMS == 3 ? j_lo : 0;
-  static constexpr int j_vol = jx * jx * jz;
+  // LDS strides, in elements, of the two regions: field (1, es, ep), current
+  // (ja, jb, jc).  The sort spreads the lanes of a wavefront over the banks of
+  // one region (k_sort.hip); both regions see conflict-free lanes only if the
+  // current region's strides are those of the field region times one odd
+  // number, modulo the 16 eight-byte banks.  Equal widths (even orders) give
+  // that by themselves.  Where the widths differ the strides do it: cubic
+  // FP32 sorts by (1, 14, 196) and takes the current rows at (15, 2, 252) =
+  // -(1, 14, 4) modulo 16 (15 x + 2 y names each of the 15 x 15 samples of a
+  // plane once), linear FP32 by (1, 12, 144) with (15, 4, 240); the others pad
+  // both regions to like rows and planes.  (Replaying the sort's lane order,
+  // the cubic FP32 deposit takes 1.6 LDS passes per add instead of 3.4, the
+  // linear one 1.6 instead of 3.0; the quartic regions are padded because
+  // (1, 15, 225) leaves some residues with 1 cell of the tile and others with
+  // 14: 1.7 passes instead of 2.5.)
+  static constexpr bool sgl = sizeof(R) == 4;
+  static constexpr int es = DIMS == 2    ? (ORDER == 1 ? 24 : ORDER == 2 ? ex : 28)
+                            : ORDER == 1 ? (sgl ? ex : 13)
+                            : ORDER == 3 ? (sgl ? ex : 15)
+                                         : ex;
+  static constexpr int ep = DIMS == 2    ? es * ex
+                            : ORDER == 1 ? (sgl ? es * ex : 165)
+                            : ORDER == 3 ? (sgl ? es * ex : 211)
+                            : ORDER == 4 ? (sgl ? 248 : es * ex)
+                                         : es * ex;
+  static constexpr bool skew = DIMS == 3 && sgl && (ORDER & 1);
+  static constexpr int ja = skew ? 15 : 1;
+  static constexpr int jb = skew ? (ORDER == 1 ? 4 : 2) : DIMS == 2 ? es : jx;
+  static constexpr int jc = DIMS == 2    ? jb * jx
+                            : ORDER == 1 ? (sgl ? 240 : 181)
+                            : ORDER == 3 ? (sgl ? 252 : 227)
+                            : ORDER == 4 ? (sgl ? 248 : jb * jx)
+                                         : jb * jx;
+  static constexpr int e_vol = ep * ez;
+  static constexpr int j_vol = jc * jz;
+  static constexpr int e_cnt = ex * ex * ez, j_cnt = jx * jx * jz;  // samples
+  static_assert(es >= ex && ep >= es * (ex - 1) + ex, "field rows and planes do not overlap");
+  static_assert(jc >= ja * (jx - 1) + jb * (jx - 1) + 1, "current planes do not overlap");
+  // a row stride of jb < jx ja entries still names every sample once: ja dx =
+  // jb dy needs dy = ja / gcd >= jx
+  static_assert(skew ? (ja >= jx && ja % 2 == 1) : jb >= jx, "current rows do not overlap");
   // E/B staged in the working precision.  The current tile has 8-byte
   // cells: in the double form it accumulates with LDS double atomic adds;
   // in the single form each contribution is rounded to a 32-bit integer on
