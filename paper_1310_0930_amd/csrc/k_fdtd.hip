@@ -75,6 +75,23 @@ __device__ __forceinline__ int column_start(const FdParams& P, int t, int kc, in
   return i + P.n[0] * (j + P.n[1] * k0);
 }
 
+// One component of a curl, ha da - hb db (da: the difference along the first
+// of the two other axes, db along the second; an axis a 2D grid does not have
+// drops out).  STEP: summed term by term, the first product rounded before the
+// second is fused to it (open and 2D grids, whose laser runs amplify any change
+// of rounding); else as the compiler contracts the expression.
+template <bool STEP, bool HAS_A, bool HAS_B, typename R>
+__device__ __forceinline__ R curl_of(R ha, R da, R hb, R db) {
+  if constexpr (STEP) {
+    R acc = R(0);
+    if constexpr (HAS_A) acc += ha * da;
+    if constexpr (HAS_B) acc -= hb * db;
+    return acc;
+  } else {
+    return ha * da - hb * db;
+  }
+}
+
 // B -= h C E (forward differences).  OPEN: some axis is open; B_c is
 // staggered along the two other axes, where the last plane of an open axis is
 // outside (its wrapped neighbours are read but not used).
@@ -113,9 +130,10 @@ __global__ void __launch_bounds__(256) k_half_b(FdParams P, const R* __restrict_
       ezx = E2[idx + ip];
       eyx = E1[idx + ip];
     }
-    if (iny && inz) B0[idx] -= hy * (E2[idx + jp] - ez) - (DIMS == 3 ? hz * (ey1 - eyk) : R(0));
-    if (inx && inz) B1[idx] -= (DIMS == 3 ? hz * (ex1 - exk) : R(0)) - hx * (ezx - ez);
-    if (inx && iny) B2[idx] -= hx * (eyx - eyk) - hy * (E0[idx + jp] - exk);
+    constexpr bool Z = DIMS == 3, S = OPEN || !Z;
+    if (iny && inz) B0[idx] -= curl_of<S, true, Z, R>(hy, E2[idx + jp] - ez, hz, ey1 - eyk);
+    if (inx && inz) B1[idx] -= curl_of<S, Z, true, R>(hz, ex1 - exk, hx, ezx - ez);
+    if (inx && iny) B2[idx] -= curl_of<S, true, true, R>(hx, eyx - eyk, hy, E0[idx + jp] - exk);
     exk = ex1;
     eyk = ey1;
   }
@@ -183,6 +201,7 @@ __global__ void __launch_bounds__(256) k_advance_e(
   for (int kk = 0; kk < KC; ++kk, idx += plane) {
     const int k = k0 + kk;
     if (DIMS == 3 && KC > 1 && k >= P.n[2]) break;
+    constexpr bool Z = DIMS == 3, S = OPEN || !Z;
     const R bx = B0[idx], by = B1[idx], bz = B2[idx];
     R bzx = __shfl_up(bz, 1, 64), byx = __shfl_up(by, 1, 64);
     if (!own) {
@@ -194,19 +213,19 @@ __global__ void __launch_bounds__(256) k_advance_e(
     const int sz = OPEN && DIMS == 3 && P.open[2] ? (k == 1 ? -1 : k == P.n[2] - 2 ? 1 : 0) : 0;
     if (inx && !aty && !atz) {
       const R old = E0[idx];
-      const R nw = old + ((gy * (bz - B2[idx + jm]) - (DIMS == 3 ? gz * (by - bym) : R(0))) - dt * J0[idx]);
+      const R nw = old + (curl_of<S, true, Z, R>(gy, bz - B2[idx + jm], gz, by - bym) - dt * J0[idx]);
       E0[idx] = nw;
       if (OPEN && (sy | sz)) mur_faces<R>(E0, idx, sy, P.n[0], ky, sz, plane, kz, old, nw);
     }
     if (iny && !atx && !atz) {
       const R old = E1[idx];
-      const R nw = old + (((DIMS == 3 ? gz * (bx - bxm) : R(0)) - gx * (bz - bzx)) - dt * J1[idx]);
+      const R nw = old + (curl_of<S, Z, true, R>(gz, bx - bxm, gx, bz - bzx) - dt * J1[idx]);
       E1[idx] = nw;
       if (OPEN && (sx | sz)) mur_faces<R>(E1, idx, sx, 1, kx, sz, plane, kz, old, nw);
     }
     if (inz && !atx && !aty) {
       const R old = E2[idx];
-      const R nw = old + ((gx * (by - byx) - gy * (bx - B0[idx + jm])) - dt * J2[idx]);
+      const R nw = old + (curl_of<S, true, true, R>(gx, by - byx, gy, bx - B0[idx + jm]) - dt * J2[idx]);
       E2[idx] = nw;
       if (OPEN && (sx | sy)) mur_faces<R>(E2, idx, sx, 1, kx, sy, P.n[0], ky, old, nw);
     }
