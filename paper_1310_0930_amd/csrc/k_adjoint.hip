@@ -576,7 +576,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
   {
     constexpr int NR = (G::e_vol + G::NT - 1) / G::NT;
     R stage[NR][6];
-    stage_load<DIMS, ORDER, R, NR, G>(P, F, org, stage);
+    stage_load<DIMS, ORDER, R, NR, G>(P, F, org, stage, (int)threadIdx.x, G::NT);
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int r = threadIdx.x + k * G::NT;

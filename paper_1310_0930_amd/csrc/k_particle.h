@@ -677,16 +677,15 @@ __device__ __forceinline__ int opaque_tid() {
 
 // E and B of a tile + halo (zero outside open faces) into registers (G: the
 // region's geometry, the push tile's by default).  Each
-// thread takes region samples and loads the six components there, with the
+// thread takes region samples (first, first + step, ...) and loads the six components there, with the
 // storage offsets along each axis formed once per sample; all loads are in
 // flight together.
 template <int DIMS, int ORDER, typename R, int NR, class G = Geo<DIMS, ORDER, R>>
 __device__ inline void stage_load(const KParams<R>& P, const DFields<R>& F, const int org[3],
-                                  R (&stage)[NR][6]) {
+                                  R (&stage)[NR][6], int first, int step) {
   const int open0 = P.bc[0] == PIC_BC_OPEN, open1 = P.bc[1] == PIC_BC_OPEN;
   const int open2 = DIMS == 3 && P.bc[2] == PIC_BC_OPEN;
   const int str1 = P.n[0], str2 = P.n[0] * P.n[1];
-  const int tid = opaque_tid();
   const int bx = org[0] + G::e_lo, by = org[1] + G::e_lo, bz = org[2] + G::e_lo_z;
   if (axis_inside(bx, G::ex, P.n[0], open0) && axis_inside(by, G::ex, P.n[1], open1) &&
       (DIMS == 2 || axis_inside(bz, G::ez, P.n[2], open2))) {
@@ -694,7 +693,7 @@ __device__ inline void stage_load(const KParams<R>& P, const DFields<R>& F, cons
     const int base = (DIMS == 3 ? bz * str2 : 0) + by * str1 + bx;
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
-      const int r = tid + k * G::NT;
+      const int r = first + k * step;
 #pragma unroll
       for (int c = 0; c < 6; ++c) stage[k][c] = R(0);
       if (r < G::e_cnt) {
@@ -708,7 +707,7 @@ __device__ inline void stage_load(const KParams<R>& P, const DFields<R>& F, cons
   }
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
-    const int r = tid + k * G::NT;
+    const int r = first + k * step;
 #pragma unroll
     for (int c = 0; c < 6; ++c) stage[k][c] = R(0);
     if (r < G::e_cnt) {

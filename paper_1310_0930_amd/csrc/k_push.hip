@@ -74,6 +74,22 @@ __device__ __forceinline__ int unpack_path(int w, int* sh) {
   return w & 0xffffff;
 }
 
+// Charge-conserving current of one virtual segment of a path (none beyond
+// its last) into the LDS current tile.
+template <int DIMS, int ORDER, typename R>
+__device__ __forceinline__ void deposit_one_lds(double* s_j, int pbase, const R* jf, const R* o0,
+                                                const int* sh, const R* o1, R q, R fz, int sg) {
+  Split<DIMS, R> S;
+  split_path<DIMS, ORDER, R>(S, o0, sh, o1);
+  if (sg > S.m) return;
+  LdsCurrent<DIMS, ORDER, R> sink{s_j, pbase, s_j};
+  R xa[3], xb[3], ft;
+  int base[3];
+  segment_ends<DIMS, ORDER, R>(S, sg, xa, xb, base, ft);
+  sink.segment(base);
+  deposit_segment<DIMS, ORDER, R>(sink, jf, xa, xb, q, fz * ft);
+}
+
 // Charge-conserving current of a whole path into the LDS current tile:
 // split at the stencil-switch planes, then each virtual segment on its own
 // stencil.  fz = q v_z (2D: the out-of-plane current per unit time,
@@ -97,9 +113,16 @@ __device__ __forceinline__ void deposit_path_lds(double* s_j, int pbase, const R
 // ranges, one per XCD: a workgroup takes tiles from its own XCD's range
 // first (neighbouring tiles share halo samples in that XCD's L2; dispatch
 // places workgroup b on XCD b mod 8) and then from the other ranges in
-// turn; `xk` counts the ranges it has found used up.  A claim is one atomic
-// increment of a range counter, issued early so that its latency overlaps
-// other work, and resolved later (one thread does both).
+// turn; `xk` counts the ranges it has found used up.  The first tile is the
+// workgroup's own number within its XCD (the range counters start behind
+// those), so that it starts without waiting for an atomic; further ones are
+// claimed with one atomic increment of a range counter each, issued early so
+// that its latency overlaps other work, and resolved later (one thread does
+// both).  A workgroup whose range is used up reads the counters to find one
+// that is not: the counters share a cache line, where atomics take about 10 ns
+// each one after the other, and 512 workgroups that each tried all 8 ranges in
+// turn held the start of every 2D launch up by 45 us (512x256 quadratic FP32,
+// cold plasma: launch 80 -> 35 us).
 __device__ inline unsigned claim_issue(DevFlags* flg, int xk) {
   return xk < 8 ? atomicAdd(&flg->tile_next[(blockIdx.x + xk) & 7], 1u) : 0u;
 }
@@ -111,7 +134,14 @@ __device__ inline int claim_resolve(unsigned local, const int* __restrict__ star
   while (xk < 8) {
     const int t = (int)((blockIdx.x + xk) & 7) * per_xcd + (int)local;
     if (local >= (unsigned)per_xcd || t >= ntiles) {
-      ++xk;
+      unsigned left = 0u;  // ranges with tiles left
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int c = (int)__hip_atomic_load(&flg->tile_next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        left |= (c < per_xcd && x * per_xcd + c < ntiles ? 1u : 0u) << x;
+      }
+      do ++xk;
+      while (xk < 8 && !(left >> ((blockIdx.x + xk) & 7) & 1u));
     } else {
       beg = starts[t];
       end = starts[t + 1];
@@ -123,8 +153,11 @@ __device__ inline int claim_resolve(unsigned local, const int* __restrict__ star
 }
 
 // Claims of the re-binned pass: one counter over the destination tiles
-// listed by the sorted pass (each holds at least one particle).
-__device__ inline unsigned rb_claim_issue(DevFlags* flg) { return atomicAdd(&flg->rb_next, 1u); }
+// listed by the sorted pass (each holds at least one particle), unless there
+// are no more of them than workgroups.
+__device__ inline unsigned rb_claim_issue(DevFlags* flg) {
+  return flg->rb_m <= gridDim.x ? flg->rb_m : atomicAdd(&flg->rb_next, 1u);
+}
 __device__ inline int rb_claim_resolve(unsigned v, const DevFlags* flg, const Rebin& rb, int& beg,
                                        int& end) {
   if (v >= flg->rb_m) return -1;
@@ -146,9 +179,6 @@ __device__ __forceinline__ int cell_tile(const KParams<R>& P, const int* c3) {
 __device__ __forceinline__ long long sext48(long long x) {
   return (long long)((unsigned long long)x << 16) >> 16;
 }
-
-// First particle of batch b for this lane.
-__device__ __forceinline__ int pbase_of_batch(int pbeg, int b, int lane) { return pbeg + 64 * b + lane; }
 
 // Next batch of 64 particles of the current tile for this wavefront.
 __device__ __forceinline__ int take_batch(int* ctr) {
@@ -188,11 +218,14 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
   __shared__ int s_q[2][3];
   __shared__ int s_batch;  // next batch of the current tile
   __shared__ int s_qn;     // paths in the crossing queue
+  __shared__ int s_rank;   // wavefronts that have finished their batches
 
   const int open0 = P.bc[0] == PIC_BC_OPEN, open1 = P.bc[1] == PIC_BC_OPEN;
   const int open2 = DIMS == 3 && P.bc[2] == PIC_BC_OPEN;
   const int str1 = P.n[0], str2 = P.n[0] * P.n[1];
-  int xk = 0;           // thread 0: ranges used up
+  // thread 0: ranges used up (every one of them where each tile has a
+  // workgroup of its own)
+  int xk = gridDim.x >= 8u * (unsigned)P.per_xcd ? 8 : 0;
   unsigned claim = 0u;  // thread 0: claim in flight
   auto issue = [&]() -> unsigned {
     if constexpr (RB)
@@ -206,27 +239,44 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     else
       return claim_resolve(c, starts, flg, P.per_xcd, P.ntiles, xk, b, e);
   };
+  // the first tile (it may be empty)
+  int tile, pbeg = 0, pend = 0;
+  if constexpr (RB) {
+    if (blockIdx.x >= flg->rb_m) return;
+    tile = rb_claim_resolve(blockIdx.x, flg, rb, pbeg, pend);
+  } else {
+    const int lt = (int)(blockIdx.x >> 3);
+    tile = (int)(blockIdx.x & 7) * P.per_xcd + lt;
+    if (lt < P.per_xcd && tile < P.ntiles) {
+      pbeg = starts[tile];
+      pend = starts[tile + 1];
+    } else {
+      tile = 0;  // past the range: no particles
+    }
+  }
+  // bound of |q|: the sort's for charges per particle (fixed during a push)
+  const float qmax = __int_as_float(__builtin_amdgcn_readfirstlane(
+      __float_as_int(pa.q ? __uint_as_float(flg->qmax) : fabsf((float)P.q_const))));
+  const bool qmax_ok = qmax <= 3.0e38f;
+  // (written as the loop writes it below: with the claim passed on directly
+  // the compiler keeps ten more registers through the particle loop)
+  if (threadIdx.x == 0) claim = issue();
   if (threadIdx.x == 0) {
     int b = 0, e = 0;
-    const int t0 = resolve(issue(), b, e);
-    s_q[0][0] = t0;
-    s_q[0][1] = b;
-    s_q[0][2] = e;
-    const int t1 = t0 < 0 ? -1 : resolve(issue(), b, e);
+    const int t1 = resolve(claim, b, e);
     s_q[1][0] = t1;
     s_q[1][1] = b;
     s_q[1][2] = e;
   }
   __syncthreads();
-  int tile = __builtin_amdgcn_readfirstlane(s_q[0][0]);
-  if (tile < 0) return;
-  int pbeg = __builtin_amdgcn_readfirstlane(s_q[0][1]);
-  int pend = __builtin_amdgcn_readfirstlane(s_q[0][2]);
   constexpr int NR = (G::e_cnt + G::NT - 1) / G::NT;
   R stage[NR][6];
   int org[3];
   tile_origin<DIMS, ORDER, R>(P, tile, org);
-  stage_load<DIMS, ORDER, R, NR>(P, F, org, stage);
+  constexpr bool by_rank = sizeof(R) == 4;
+  // this thread's region samples: sfirst + k sstep
+  int sfirst = (int)threadIdx.x, sstep = G::NT;
+  stage_load<DIMS, ORDER, R, NR>(P, F, org, stage, sfirst, sstep);
   for (int idx = threadIdx.x; idx < 3 * G::j_vol; idx += G::NT) s_j[idx] = 0.0;
 
   // the staged fields of the next tile from registers into LDS
@@ -234,7 +284,7 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     const int tid = opaque_tid();
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
-      const int r = tid + k * G::NT;
+      const int r = by_rank ? sfirst + k * sstep : tid + k * G::NT;
       if (r < G::e_cnt) {
         const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
         const int e = lz * G::ep + ly * G::es + lx;
@@ -258,6 +308,7 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     if (threadIdx.x == 0) {
       s_batch = 0;
       s_qn = 0;
+      s_rank = 0;
       if (next >= 0) claim = issue();  // for tile i+2
     }
 
@@ -277,10 +328,8 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     R jf[3] = {P.jfac[0], P.jfac[1], P.jfac[2]};
     R zs = R(1);
     int Ks[3] = {0, 0, 0};
-    const float qmax = pa.q ? __uint_as_float(flg->qmax) : fabsf((float)P.q_const);
-    const bool qmax_ok = qmax <= 3.0e38f;
     if constexpr (G::fixed) {
-      const unsigned ncontrib = (unsigned)(DIMS + 1) * (unsigned)(pend - pbeg);
+      const unsigned ncontrib = (unsigned)(DIMS + 1) * (unsigned)max(pend - pbeg, 1);
       const int g = 32 - __clz((int)(ncontrib - 1u));  // ncontrib <= 2^g
       const int top = 47 - g;
 #pragma unroll
@@ -307,31 +356,45 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
       s_q[it & 1][2] = e;
     }
     const int lane = threadIdx.x & 63;
-    // The crossing queue, whole 64-path rounds dealt round-robin to the
-    // wavefronts; every lane splits its path and deposits all of its
-    // segments.  It is drained after the barrier that ends the tile's
-    // batches, once the next tile's fields (loaded meanwhile) are in LDS.
+    // The crossing queue is drained after the barrier that ends the tile's
+    // batches, once the next tile's fields (loaded meanwhile) are in LDS, in
+    // rounds dealt round-robin to the wavefronts.  2D: 64 paths a round, every
+    // lane splits its path and deposits all of its segments.  3D: 16 paths a
+    // round, four lanes per path, each deposits one of its (at most four)
+    // segments; the lanes of a path are 16 apart, because the LDS serves
+    // eight-byte atomics 16 lanes at a time and a path's lanes mostly add to
+    // the same samples.  A warm 3D tile's 140 paths are then one round of
+    // nine wavefronts that lasts a segment instead of one of three that lasts
+    // the longest path (128^3 FP32, 20 steps: 20.96 -> 20.63 ms; the 512x256
+    // laser, whose tiles queue hundreds of paths, 2.51 -> 2.57 ms).  (Early
+    // finishers draining while others still push was slower: the adds go to
+    // unsorted cells and slow the batches they run beside.)
+    constexpr int QL = DIMS == 3 ? 4 : 1;  // lanes per path
     auto drain = [&](int total) {
-      for (int r0 = (threadIdx.x >> 6) * 64; r0 < total; r0 += G::NT) {
-        const int r = r0 + lane;
+      for (int r0 = (int)(threadIdx.x >> 6) * (64 / QL); r0 < total; r0 += G::NT / QL) {
+        const int r = r0 + lane % (64 / QL);
         if (r < total) {
           int shq[3];
           const int pb = unpack_path(q_path[r], shq);
-          R a0[3] = {R(0), R(0), R(0)}, a1[3] = {R(0), R(0), R(0)};
+          R a0[3] = {R(0), R(0), R(0)}, a1[3] = {R(0), R(0), R(0)}, qr, fr;
 #pragma unroll
           for (int d = 0; d < DIMS; ++d) a0[d] = q_o0[d][r];
           if constexpr (Q::compact) {
             const int pp = q_idx[r];
 #pragma unroll
             for (int d = 0; d < 3; ++d) a1[d] = pa.off[d][pp];
-            deposit_path_lds<DIMS, ORDER, R>(s_j, pb, jf, a0, shq, a1,
-                                             pa.q ? pa.q[pp] : P.q_const, R(0));
+            qr = pa.q ? pa.q[pp] : P.q_const;
+            fr = R(0);
           } else {
 #pragma unroll
             for (int d = 0; d < DIMS; ++d) a1[d] = q_val[d][r];
-            deposit_path_lds<DIMS, ORDER, R>(s_j, pb, jf, a0, shq, a1, q_val[DIMS][r],
-                                             q_val[DIMS + 1][r]);
+            qr = q_val[DIMS][r];
+            fr = q_val[DIMS + 1][r];
           }
+          if constexpr (QL == 1)
+            deposit_path_lds<DIMS, ORDER, R>(s_j, pb, jf, a0, shq, a1, qr, fr);
+          else
+            deposit_one_lds<DIMS, ORDER, R>(s_j, pb, jf, a0, shq, a1, qr, fr, lane / (64 / QL));
         }
       }
     };
@@ -341,19 +404,19 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     // past the end are idle) so that the queue's ballot sees every lane.
     // The next batch is taken, and its particle state loaded, one iteration
     // ahead.
-    // (p: position in the tile's range; pi: the particle, through the list
-    // in the re-binned pass)
-    int p = pbase_of_batch(pbeg, take_batch(&s_batch), lane), pn;
-    int qn = RB ? (p < pend ? rb.list[p] : 0) : p;
+    // (The loop runs on the batch's first position, a scalar; pi: the
+    // particle, through the list in the re-binned pass.)
+    int b0 = pbeg + 64 * take_batch(&s_batch), bn;
+    int qn = RB ? (b0 + lane < pend ? rb.list[b0 + lane] : 0) : b0 + lane;
     PState<R> nxt;
-    if (p < pend) nxt = load_particle<DIMS, R>(pa, qn, P.q_const);
-    for (; p - lane < pend; p = pn) {
+    if (b0 + lane < pend) nxt = load_particle<DIMS, R>(pa, qn, P.q_const);
+    for (; b0 < pend; b0 = bn) {
       const int pi = qn;
       PState<R> s = nxt;
-      pn = pbase_of_batch(pbeg, take_batch(&s_batch), lane);
-      qn = RB ? (pn < pend ? rb.list[pn] : 0) : pn;
-      if (pn < pend) nxt = load_particle<DIMS, R>(pa, qn, P.q_const);
-      bool valid = p < pend && s.cl >= 0;
+      bn = pbeg + 64 * take_batch(&s_batch);
+      qn = RB ? (bn + lane < pend ? rb.list[bn + lane] : 0) : bn + lane;
+      if (bn + lane < pend) nxt = load_particle<DIMS, R>(pa, qn, P.q_const);
+      bool valid = b0 + lane < pend && s.cl >= 0;
       int c3[3] = {0, 0, 0};
       if (valid) valid = decode<DIMS, R>(P, s, c3, flg);
       // position relative to the tile origin (periodic image inside the window)
@@ -455,7 +518,19 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     if (nt >= 0) {  // the next tile's fields, in flight during the flush
       int norg[3];
       tile_origin<DIMS, ORDER, R>(P, nt, norg);
-      stage_load<DIMS, ORDER, R, NR>(P, F, norg, stage);
+      // in the order the wavefronts finish, NR runs of 64 samples each: the
+      // last ones, which the others wait for, have none to load
+      // (128^3 quadratic FP32: push 816 -> 806 us)
+      // (in single precision; double spills its registers to it)
+      if constexpr (by_rank) {
+        int rank = 0;
+        if (opaque_tid() % 64 == 0) rank = atomicAdd(&s_rank, 1);
+        sfirst = __builtin_amdgcn_readfirstlane(rank) * (64 * NR) + lane;
+        sstep = 64;
+      } else {
+        sfirst = opaque_tid();
+      }
+      stage_load<DIMS, ORDER, R, NR>(P, F, norg, stage, sfirst, by_rank ? 64 : G::NT);
     } else {  // (defining stage on both paths ends the current values' life here)
 #pragma unroll
       for (int k = 0; k < NR; ++k)
@@ -663,19 +738,23 @@ __global__ void __launch_bounds__(256) k_push_deferred(KParams<R> P, DParts<R> p
 }
 
 // Zero J (n = 0: keep it, another species adds its current), the
-// deferred-list lengths, the tile counters and the re-binned pass's counts
-// before a push.
+// deferred-list lengths and the re-binned pass's counts before a push, and set
+// the tile counters behind the first tiles of the two tile passes' workgroups
+// (grid and rb_grid of them).
 template <typename R>
-__global__ void k_push_prologue(R* a, R* b, R* c, long n, DevFlags* flg, int* rb_cnt, int ntiles) {
+__global__ void k_push_prologue(R* a, R* b, R* c, long n, DevFlags* flg, int* rb_cnt, int ntiles,
+                                unsigned grid, unsigned rb_grid) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     flg->since_sort += flg->ndefer;
     flg->ndefer = 0u;
     flg->ndefer2 = 0u;
     flg->rb_m = 0u;
-    flg->rb_next = 0u;
+    flg->rb_next = rb_grid;
     flg->rb_done = 0u;
   }
-  if (blockIdx.x == 0 && threadIdx.x < 8) flg->tile_next[threadIdx.x] = 0u;
+  // every workgroup starts with a tile of its own
+  if (blockIdx.x == 0 && threadIdx.x < 8)
+    flg->tile_next[threadIdx.x] = (grid + 7u - threadIdx.x) / 8u;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ntiles; i += gridDim.x * blockDim.x)
     rb_cnt[i] = 0;
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
@@ -699,7 +778,7 @@ static int device_cus() {
 }
 
 // Workgroups of the persistent tile kernel: as many as are resident at once
-// (compute units x workgroups per unit), at most 8 x the XCD range length.
+// (compute units x workgroups per unit), at most one per tile.
 template <int DIMS, int ORDER, typename R, bool RB>
 static unsigned tile_grid(const KParams<R>& P) {
   using G = Geo<DIMS, ORDER, R>;
@@ -751,14 +830,16 @@ static int launch_pd(const pic_ctx* ctx, const pic_particles* p, const pic_field
   const long ncell = accumulate ? 0L : (long)P.n[0] * P.n[1] * P.n[2];
   const long nz = ncell > P.ntiles ? ncell : (long)P.ntiles;
   const long fb = (nz + 255) / 256;
+  const unsigned grid = tile_grid<DIMS, ORDER, R, false>(P);
+  const unsigned rb_grid = ctx->rebin ? tile_grid<DIMS, ORDER, R, true>(P) : 0u;
   k_push_prologue<R><<<dim3((unsigned)(fb < 1 ? 1 : fb < 4096 ? fb : 4096)), dim3(256), 0, s>>>(
-      F.J[0], F.J[1], F.J[2], ncell, flg, rb.cnt, P.ntiles);
-  k_push_tile<DIMS, ORDER, R, false><<<dim3(tile_grid<DIMS, ORDER, R, false>(P)), dim3(G::NT), 0, s>>>(
+      F.J[0], F.J[1], F.J[2], ncell, flg, rb.cnt, P.ntiles, grid, rb_grid);
+  k_push_tile<DIMS, ORDER, R, false><<<dim3(grid), dim3(G::NT), 0, s>>>(
       P, pa, F, (const int*)(w + L.starts), deferred, flg, rb);
   if (ctx->rebin) {
     k_rebin_count<DIMS, ORDER, R><<<dim3(256), dim3(RB_NT), 0, s>>>(P, pa.cell, deferred, rb, flg);
     k_rebin_scatter<DIMS, ORDER, R><<<dim3(512), dim3(256), 0, s>>>(P, pa.cell, deferred, rb, flg);
-    k_push_tile<DIMS, ORDER, R, true><<<dim3(tile_grid<DIMS, ORDER, R, true>(P)), dim3(G::NT), 0, s>>>(
+    k_push_tile<DIMS, ORDER, R, true><<<dim3(rb_grid), dim3(G::NT), 0, s>>>(
         P, pa, F, (const int*)(w + L.starts), deferred, flg, rb);
     k_push_deferred<DIMS, ORDER, R><<<dim3(1024), dim3(256), 0, s>>>(P, pa, F, rb.defer2, &flg->ndefer2,
                                                                       flg);
