@@ -1,6 +1,6 @@
 // Hand-written adjoint (vector-Jacobian product) of one gather + Boris push +
-// move + split + Esirkepov deposit pass: one thread per particle in global
-// memory, or in 2D out of LDS per tile of sorted particles.
+// move + split + Esirkepov deposit pass: out of LDS per tile of sorted
+// particles, or one thread per particle in global memory.
 //
 // Given the adjoints of the step's outputs -- lamX^{n+1} (positions, in cell
 // units), lamU^{n+1/2} (momenta) and lamJ^{n+1/2} (the current, produced by
@@ -58,11 +58,13 @@ __device__ __forceinline__ int sample_index(const KParams<R>& P, int dims, bool 
   return ix + P.n[0] * (iy + P.n[1] * iz);
 }
 
-// Sample access of the adjoint helpers, at lattice coordinates: E^n/B^n
-// (read), lamE/lamB (added to) and lamJ (read).  AdjGlobal goes to the
-// global arrays with the domain's wrap and open faces; AdjLds to a tile's
-// LDS regions (coordinates relative to the tile origin), the lamE/lamB
-// region accumulating in double.
+// Sample access of the adjoint helpers.  ref(comp, first) fixes the first
+// stencil node of a field component (0..2 E, 3..5 B), at(r, i, j, k) reads the
+// field and add(r, i, j, k, v) adds to its adjoint at compile-time offsets from
+// it; jref and jat do the same for lamJ.  AdjGlobal goes to the global arrays
+// with the domain's wrap and open faces; AdjLds to a tile's LDS regions
+// (coordinates relative to the tile origin), the lamE/lamB region accumulating
+// in double.
 template <int DIMS, typename R>
 struct AdjGlobal {
   const KParams<R>& P;
@@ -70,37 +72,62 @@ struct AdjGlobal {
   R* const* lamE;
   R* const* lamB;
   R* const* lamJ;
-  // adds v to the adjoint of sample (isb, c, x, y, z) and returns the field there
-  __device__ __forceinline__ R field_add(bool isb, int c, int x, int y, int z, R v) const {
-    const int g = sample_index<R>(P, DIMS, isb, c, x, y, z);
-    if (g < 0) return R(0);
-    atomicAdd(&(isb ? lamB : lamE)[c][g], v);
-    return (isb ? F.B : F.E)[c][g];
+  struct Ref {
+    int comp, x, y, z;
+  };
+  __device__ __forceinline__ Ref ref(int comp, const int* b) const { return {comp, b[0], b[1], b[2]}; }
+  __device__ __forceinline__ int index(const Ref& r, int i, int j, int k) const {
+    return sample_index<R>(P, DIMS, r.comp >= 3, r.comp % 3, r.x + i, r.y + j, r.z + k);
   }
-  __device__ __forceinline__ R lamj(int c, int x, int y, int z) const {
-    const int g = sample_index<R>(P, DIMS, false, c, x, y, z);
-    return g < 0 ? R(0) : lamJ[c][g];
+  __device__ __forceinline__ R at(const Ref& r, int i, int j, int k) const {
+    const int g = index(r, i, j, k);
+    return g < 0 ? R(0) : (r.comp >= 3 ? F.B[r.comp - 3] : F.E[r.comp])[g];
+  }
+  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R v) const {
+    const int g = index(r, i, j, k);
+    if (g >= 0) atomicAdd(&(r.comp >= 3 ? lamB[r.comp - 3] : lamE[r.comp])[g], v);
+  }
+  __device__ __forceinline__ Ref jref(int comp, const int* b) const { return ref(comp, b); }
+  __device__ __forceinline__ R jat(const Ref& r, int i, int j, int k) const {
+    const int g = index(r, i, j, k);
+    return g < 0 ? R(0) : lamJ[r.comp][g];
   }
 };
 
+// Phases of the LDS adjoint.  In 2D one kernel does a particle's whole step
+// (PDA_ALL).  In 3D a tile's E/B, lamJ and lamE/lamB (in double) together
+// exceed a CU's LDS, and one particle's whole step needs more than 200
+// registers, so that a CU held 8 wavefronts and neither its LDS nor its
+// arithmetic was half used (96x80x64 quadratic FP32: 1237 us); there PDA_BACK
+// goes from the step's outputs back to the adjoints of the interpolated fields
+// (E/B and lamJ in LDS; 262 us, the VALU 73 % busy) and leaves those six values
+// in scratch, and PDA_GATHER transposes the gather (E/B and lamE/lamB in LDS;
+// 535 us, the LDS 69 % busy: 162 double adds of at least 8 LDS cycles per
+// 64 particles).
+enum { PDA_ALL = 0, PDA_BACK = 1, PDA_GATHER = 2 };
+
 // Region of one workgroup of the LDS adjoint: the push tile, cut along z
-// into S slabs when the three regions (E/B and lamJ in the working
+// into S slabs when the phase's regions (E/B and lamJ in the working
 // precision, lamE/lamB in double) of a whole 3D tile exceed a CU's LDS.
 // Each slab keeps the tile's drift allowance and stencil reach; x and y are
-// the tile's.  `fits` is false where even one-cell slabs do not fit (cubic
-// in double precision), and that form keeps the global-memory kernel.
-template <int DIMS, int ORDER, typename R>
+// the tile's.
+template <int DIMS, int ORDER, typename R, int PHASE>
 struct AdjGeo : Geo<DIMS, ORDER, R> {
   using B = Geo<DIMS, ORDER, R>;
   using Rc = typename B::Rc;
+  static constexpr bool has_lj = PHASE != PDA_GATHER, has_leb = PHASE != PDA_BACK;
   static constexpr size_t bytes(int tz) {
-    return (sizeof(R) * 6 + sizeof(double) * 6) * (size_t)(B::ex * B::ex * (tz + 2 * B::AZ + Rc::g_hi - Rc::g_lo)) +
-           sizeof(R) * 3 * (size_t)(B::jx * B::jx * (tz + 2 * B::AZ + Rc::d_hi - Rc::d_lo));
+    return (sizeof(R) * 6 + (has_leb ? sizeof(double) * 6 : 0)) *
+               (size_t)(B::ex * B::ex * (tz + 2 * B::AZ + Rc::g_hi - Rc::g_lo)) +
+           (has_lj ? sizeof(R) * 3 * (size_t)(B::jx * B::jx * (tz + 2 * B::AZ + Rc::d_hi - Rc::d_lo)) : 0);
   }
   static constexpr size_t LDS_MAX = 160 * 1024;
-  // 2D: several workgroups share a CU; 3D: one per CU, 8 wavefronts of up
-  // to 256 VGPRs
-  static constexpr int NT = DIMS == 2 ? 256 : 512;
+  // the gather's transpose needs few registers: 16 wavefronts in FP32
+  static constexpr int NT = PHASE == PDA_GATHER && sizeof(R) == 4 ? 1024 : 512;
+  // wavefronts per SIMD to keep registers for: up to quadratic order in FP32
+  // two workgroups of PDA_BACK share a CU (in 2D, where there are 512 tiles for
+  // 256 CUs, the spills cost more: 512x256 quadratic FP32 138 against 129 us)
+  static constexpr int WPE = PHASE == PDA_BACK && sizeof(R) == 4 && ORDER <= 2 ? 4 : 1;
   // with several slabs each wavefront queues the particles of its slab:
   // 128 indices per wavefront
   static constexpr int QCAP = 128;
@@ -112,8 +139,8 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
     return 0;
   }
   static constexpr int S = pick();
-  static constexpr bool fits = S > 0;
-  static constexpr int TZ = fits ? B::TZ / S : 1;
+  static_assert(S > 0, "one-cell slabs fit");
+  static constexpr int TZ = B::TZ / S;
   static constexpr int ez = DIMS == 3 ? TZ + 2 * B::AZ + Rc::g_hi - Rc::g_lo : 1;
   static constexpr int es = B::ex, ep = B::ex * B::ex;
   static constexpr int e_vol = ep * ez, e_cnt = e_vol;
@@ -123,73 +150,126 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
 
 template <int DIMS, int ORDER, typename R, class G>
 struct AdjLds {
-  const R* eb;   // E^n (0..2), B^n (3..5) over the field region
-  const R* lj;   // lamJ over the current region
-  double* leb;   // lamE (0..2), lamB (3..5) over the field region
-  __device__ __forceinline__ R field_add(bool isb, int c, int x, int y, int z, R v) const {
-    const int i = (DIMS == 3 ? (z - G::e_lo_z) * G::ex : 0) * G::ex + (y - G::e_lo) * G::ex +
-                  (x - G::e_lo) + (isb ? 3 + c : c) * G::e_vol;
-    atomicAdd(&leb[i], (double)v);
-    return eb[i];
+  lds_ptr<const R> eb;   // E^n (0..2), B^n (3..5) over the field region
+  lds_ptr<const R> lj;   // lamJ over the current region
+  lds_ptr<double> leb;   // lamE (0..2), lamB (3..5) over the field region
+  struct Ref {
+    lds_ptr<const R> f;
+    lds_ptr<double> l;
+  };
+  template <typename T>
+  static __device__ __forceinline__ lds_ptr<T> pin(lds_ptr<T> p) {
+    uint32_t a = (uint32_t)(uintptr_t)p;
+    asm volatile("" : "+v"(a));
+    return (lds_ptr<T>)(uintptr_t)a;
   }
-  __device__ __forceinline__ R lamj(int c, int x, int y, int z) const {
-    return lj[(DIMS == 3 ? (z - G::j_lo_z) * G::jx : 0) * G::jx + (y - G::j_lo) * G::jx +
-              (x - G::j_lo) + c * G::j_vol];
+  // one register per array, so that every access is an immediate offset
+  __device__ __forceinline__ Ref ref(int comp, const int* b) const {
+    const int i = (DIMS == 3 ? (b[2] - G::e_lo_z) * G::ep : 0) + (b[1] - G::e_lo) * G::es +
+                  (b[0] - G::e_lo) + comp * G::e_vol;
+    return {pin<const R>(eb + i), pin<double>(leb + i)};
+  }
+  // single reads, as in the push's gather
+  __device__ __forceinline__ R at(const Ref& r, int i, int j, int k) const {
+    using vptr = __attribute__((address_space(3))) const volatile R*;
+    return ((vptr)r.f)[k * G::ep + j * G::es + i];
+  }
+  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R v) const {
+    __hip_atomic_fetch_add(&r.l[k * G::ep + j * G::es + i], (double)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __device__ __forceinline__ lds_ptr<const R> jref(int comp, const int* b) const {
+    return pin<const R>(lj + (DIMS == 3 ? (b[2] - G::j_lo_z) * G::jx * G::jx : 0) +
+                        (b[1] - G::j_lo) * G::jx + (b[0] - G::j_lo) + comp * G::j_vol);
+  }
+  __device__ __forceinline__ R jat(lds_ptr<const R> r, int i, int j, int k) const {
+    using vptr = __attribute__((address_space(3))) const volatile R*;
+    return ((vptr)r)[(k * G::jx + j) * G::jx + i];
   }
 };
 
-// Transpose of the gather: lamF[node] += w lamFp for every stencil node and
-// lamX += sum (dw/dX) F lamFp.
+// Transpose of the gather of component COMP, whose weights and their
+// derivatives per axis are w and dw, from its first stencil node: every node's
+// adjoint receives w lam, and lX the derivative of the interpolated value times
+// lam.  The sums over the stencil are nested (x, then y, then z), two products
+// per sample.
+template <int DIMS, int ORDER, typename R, class Acc>
+__device__ __forceinline__ void gather_vjp_comp(const Acc& ac, int comp, const int* first,
+                                                const R (*w)[ORDER + 1], const R (*dw)[ORDER + 1],
+                                                R lam, R* lX) {
+  constexpr int M = ORDER + 1;
+  constexpr int MZ = DIMS == 3 ? M : 1;
+  const auto r = ac.ref(comp, first);
+  R g[3] = {R(0), R(0), R(0)};
+#pragma unroll
+  for (int k = 0; k < MZ; ++k) {
+    R s = R(0), dy = R(0), dx = R(0);
+    const R lz = DIMS == 3 ? w[2][k] * lam : lam;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      R sx = R(0), dxx = R(0);
+      const R lyz = w[1][j] * lz;
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const R f = ac.at(r, i, j, k);
+        sx += w[0][i] * f;
+        dxx += dw[0][i] * f;
+        ac.add(r, i, j, k, w[0][i] * lyz);
+      }
+      s += w[1][j] * sx;
+      dy += dw[1][j] * sx;
+      dx += w[1][j] * dxx;
+    }
+    g[0] += (DIMS == 3 ? w[2][k] : R(1)) * dx;
+    g[1] += (DIMS == 3 ? w[2][k] : R(1)) * dy;
+    if (DIMS == 3) g[2] += dw[2][k] * s;
+  }
+#pragma unroll
+  for (int d = 0; d < DIMS; ++d) lX[d] += lam * g[d];
+}
+
+// Transpose of the gather over the six components.
 template <int DIMS, int ORDER, typename R, class Acc>
 __device__ __forceinline__ void gather_vjp(const Acc& ac, const int* c3, const R* o, const R* lEp,
                                            const R* lBp, R* lX) {
   constexpr int M = ORDER + 1;
-  constexpr int MZ = DIMS == 3 ? M : 1;
   R wn[3][M], ws[3][M], dn[3][M], dsg[3][M];
-  int bn[3] = {0, 0, 0}, bs[3] = {0, 0, 0};
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int i = 0; i < M; ++i) wn[d][i] = ws[d][i] = dn[d][i] = dsg[d][i] = R(0);
+  int bn[3] = {c3[0], c3[1], c3[2]}, bs[3] = {c3[0], c3[1], c3[2]};
 #pragma unroll
   for (int d = 0; d < DIMS; ++d) {
     R xi;
-    bn[d] = piece_node<ORDER>(o[d], xi) - ORDER / 2;
+    bn[d] += piece_node<ORDER>(o[d], xi) - ORDER / 2;
     shape<ORDER>(xi, wn[d]);
     shape_deriv<ORDER>(xi, dn[d]);
-    bs[d] = piece_stag<ORDER>(o[d], xi) - ORDER / 2;
+    bs[d] += piece_stag<ORDER>(o[d], xi) - ORDER / 2;
     shape<ORDER>(xi, ws[d]);
     shape_deriv<ORDER>(xi, dsg[d]);
   }
-  if (DIMS == 2) {
-    wn[2][0] = ws[2][0] = R(1);
-  }
-  for (int comp = 0; comp < 6; ++comp) {
-    const bool isb = comp >= 3;
-    const int c = isb ? comp - 3 : comp;
-    const R lam = isb ? lBp[c] : lEp[c];
-    const R(*w[3])[M];
-    const R(*dw[3])[M];
-    int b[3];
+  auto one = [&](auto comp_c) {
+    constexpr int comp = decltype(comp_c)::value;
+    constexpr bool isb = comp >= 3;
+    constexpr int c = isb ? comp - 3 : comp;
+    R w[3][M], dw[3][M];
+    int first[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < 3; ++d) {  // staggered along c (E_c), along the two others (B_c)
       const bool st = isb ? (d != c) : (d == c);
-      w[d] = st ? &ws[d] : &wn[d];
-      dw[d] = st ? &dsg[d] : &dn[d];
-      b[d] = st ? bs[d] : bn[d];
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        if (d >= DIMS) continue;
+        w[d][i] = st ? ws[d][i] : wn[d][i];
+        dw[d][i] = st ? dsg[d][i] : dn[d][i];
+      }
+      first[d] = st ? bs[d] : bn[d];
     }
-    for (int k = 0; k < MZ; ++k)
-      for (int j = 0; j < M; ++j)
-        for (int i = 0; i < M; ++i) {
-          const R wx = (*w[0])[i], wy = (*w[1])[j], wz = (*w[2])[k];
-          const R fl = ac.field_add(isb, c, c3[0] + b[0] + i, c3[1] + b[1] + j, c3[2] + b[2] + k,
-                                    wx * wy * wz * lam) *
-                       lam;
-          lX[0] += (*dw[0])[i] * wy * wz * fl;
-          lX[1] += wx * (*dw[1])[j] * wz * fl;
-          if (DIMS == 3) lX[2] += wx * wy * (*dw[2])[k] * fl;
-        }
-  }
+    gather_vjp_comp<DIMS, ORDER, R>(ac, comp, first, w, dw, isb ? lBp[c] : lEp[c], lX);
+  };
+  one(std::integral_constant<int, 0>{});
+  one(std::integral_constant<int, 1>{});
+  one(std::integral_constant<int, 2>{});
+  one(std::integral_constant<int, 3>{});
+  one(std::integral_constant<int, 4>{});
+  one(std::integral_constant<int, 5>{});
 }
 
 // Transpose of the Boris step u -> u' under (Ep, Bp), recomputing its
@@ -265,118 +345,95 @@ __device__ __forceinline__ void deposit_segment_vjp(const KParams<R>& P, const A
                                                     const R* xb, R q, R fz, R* lxa, R* lxb,
                                                     R& lfz) {
   constexpr int M = ORDER + 1;
-  constexpr int MZ = DIMS == 3 ? M : 1;
-  R S0[3][M], dS[3][M], Sm[3][M], d12[3][M];
-  R lS0[3][M], ldS[3][M], lSm[3][M], ld12[3][M];
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      S0[d][i] = dS[d][i] = Sm[d][i] = d12[d][i] = R(0);
-      lS0[d][i] = ldS[d][i] = lSm[d][i] = ld12[d][i] = R(0);
-    }
+  constexpr R twelfth = R(1.0 / 12.0);
+  // mean weights Sm = S0 + dS/2 and differences dS; the transverse factor is
+  // A = Sm_a Sm_b + dS_a dS_b / 12
+  R Sm[DIMS][M], dS[DIMS][M], lSm[DIMS][M], ldS[DIMS][M];
 #pragma unroll
   for (int d = 0; d < DIMS; ++d) {
-    shape<ORDER>(xa[d], S0[d]);
+    shape<ORDER>(xa[d], Sm[d]);
     dshape<ORDER>(xa[d], xb[d], dS[d]);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      Sm[d][i] = S0[d][i] + R(0.5) * dS[d][i];
-      d12[d][i] = R(1.0 / 12.0) * dS[d][i];
+      Sm[d][i] += R(0.5) * dS[d][i];
+      lSm[d][i] = ldS[d][i] = R(0);
     }
   }
+  const int first[3] = {c3[0] + base[0], c3[1] + base[1], c3[2] + base[2]};
   lfz = R(0);
-  auto lam_at = [&](int comp, int i, int j, int k) -> R {
-    return ac.lamj(comp, c3[0] + base[0] + i, c3[1] + base[1] + j, c3[2] + base[2] + k);
-  };
-  (void)MZ;
-  if (DIMS == 3) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int a = (c + 1) % 3, b = (c + 2) % 3;
-      const R qj = q * P.jfac[c];
-      R Pc[ORDER], lP[ORDER];
-      R run = R(0);
+  for (int c = 0; c < DIMS; ++c) {
+    const int a = (c + 1) % DIMS, b = DIMS == 3 ? (c + 2) % 3 : a;
+    const R qj = q * P.jfac[c];
+    R Pc[ORDER], lP[ORDER];
+    R run = R(0);
 #pragma unroll
-      for (int i = 0; i < ORDER; ++i) {
-        run += dS[c][i];
-        Pc[i] = qj * run;
-        lP[i] = R(0);
-      }
-#pragma unroll
-      for (int ib = 0; ib < M; ++ib)
-#pragma unroll
-        for (int ia = 0; ia < M; ++ia) {
-          const R A = Sm[a][ia] * Sm[b][ib] + d12[a][ia] * dS[b][ib];
-          R lA = R(0);
-#pragma unroll
-          for (int ic = 0; ic < ORDER; ++ic) {
-            int L[3];
-            L[c] = ic;
-            L[a] = ia;
-            L[b] = ib;
-            const R g = lam_at(c, L[0], L[1], L[2]);
-            lA += g * Pc[ic];
-            lP[ic] += g * A;
-          }
-          lSm[a][ia] += lA * Sm[b][ib];
-          lSm[b][ib] += lA * Sm[a][ia];
-          ld12[a][ia] += lA * dS[b][ib];
-          ldS[b][ib] += lA * d12[a][ia];
-        }
-      // P_c[ic] = qj * sum_{i <= ic} dS_c[i]
-      R acc = R(0);
-#pragma unroll
-      for (int i = ORDER - 1; i >= 0; --i) {
-        acc += lP[i];
-        ldS[c][i] += qj * acc;
-      }
+    for (int i = 0; i < ORDER; ++i) {
+      run += dS[c][i];
+      Pc[i] = qj * run;
+      lP[i] = R(0);
     }
-  } else {
+    const auto r = ac.jref(c, first);
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int a = 1 - c;
-      const R qj = q * P.jfac[c];
-      R Pc[ORDER], lP[ORDER];
-      R run = R(0);
+    for (int ib = 0; ib < (DIMS == 3 ? M : 1); ++ib) {
+      const R sb = DIMS == 3 ? Sm[b][ib] : R(1);
+      const R db = DIMS == 3 ? twelfth * dS[b][ib] : R(0);
+      R ls = R(0), ld = R(0);  // sums over ia for axis b
 #pragma unroll
-      for (int i = 0; i < ORDER; ++i) {
-        run += dS[c][i];
-        Pc[i] = qj * run;
-        lP[i] = R(0);
-      }
-#pragma unroll
-      for (int ia = 0; ia < M; ++ia)
+      for (int ia = 0; ia < M; ++ia) {
+        const R A = DIMS == 3 ? Sm[a][ia] * sb + dS[a][ia] * db : Sm[a][ia];
+        R lA = R(0);
 #pragma unroll
         for (int ic = 0; ic < ORDER; ++ic) {
-          int L[2];
+          int L[3] = {0, 0, 0};
           L[c] = ic;
           L[a] = ia;
-          const R g = lam_at(c, L[0], L[1], 0);
-          lSm[a][ia] += g * Pc[ic];
-          lP[ic] += g * Sm[a][ia];
+          if (DIMS == 3) L[b] = ib;
+          const R g = ac.jat(r, L[0], L[1], L[2]);
+          lA += g * Pc[ic];
+          lP[ic] += g * A;
         }
-      R acc = R(0);
-#pragma unroll
-      for (int i = ORDER - 1; i >= 0; --i) {
-        acc += lP[i];
-        ldS[c][i] += qj * acc;
+        lSm[a][ia] += lA * sb;
+        if (DIMS == 3) {
+          ldS[a][ia] += lA * db;
+          ls += lA * Sm[a][ia];
+          ld += lA * dS[a][ia];
+        }
+      }
+      if (DIMS == 3) {
+        lSm[b][ib] += ls;
+        ldS[b][ib] += twelfth * ld;
       }
     }
+    // P_c[ic] = qj * sum_{i <= ic} dS_c[i]
+    R acc = R(0);
 #pragma unroll
-    for (int j = 0; j < M; ++j)
+    for (int i = ORDER - 1; i >= 0; --i) {
+      acc += lP[i];
+      ldS[c][i] += qj * acc;
+    }
+  }
+  if (DIMS == 2) {  // the out-of-plane current
+    const auto r = ac.jref(2, first);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      const R dj = twelfth * dS[1][j];
+      R ls = R(0), ld = R(0);
 #pragma unroll
       for (int i = 0; i < M; ++i) {
-        const R g = lam_at(2, i, j, 0);
-        const R W = Sm[0][i] * Sm[1][j] + d12[0][i] * dS[1][j];
-        lfz += g * W;
-        lSm[0][i] += g * fz * Sm[1][j];
-        lSm[1][j] += g * fz * Sm[0][i];
-        ld12[0][i] += g * fz * dS[1][j];
-        ldS[1][j] += g * fz * d12[0][i];
+        const R g = ac.jat(r, i, j, 0);
+        lfz += g * (Sm[0][i] * Sm[1][j] + dS[0][i] * dj);
+        const R gf = g * fz;
+        lSm[0][i] += gf * Sm[1][j];
+        ldS[0][i] += gf * dj;
+        ls += gf * Sm[0][i];
+        ld += gf * dS[0][i];
       }
+      lSm[1][j] += ls;
+      ldS[1][j] += twelfth * ld;
+    }
   }
-  // Sm = S0 + dS/2, d12 = dS/12, S0 = S(xa), dS = S(xb) - S(xa)
+  // Sm = S(xa) + dS/2, dS = S(xb) - S(xa)
 #pragma unroll
   for (int d = 0; d < DIMS; ++d) {
     R da[M], db[M];
@@ -385,10 +442,9 @@ __device__ __forceinline__ void deposit_segment_vjp(const KParams<R>& P, const A
     R la = R(0), lb = R(0);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      lS0[d][i] += lSm[d][i];
-      ldS[d][i] += R(0.5) * lSm[d][i] + R(1.0 / 12.0) * ld12[d][i];
-      la += (lS0[d][i] - ldS[d][i]) * da[i];
-      lb += ldS[d][i] * db[i];
+      const R l = ldS[d][i] + R(0.5) * lSm[d][i];
+      la += (lSm[d][i] - l) * da[i];
+      lb += l * db[i];
     }
     lxa[d] = la;
     lxb[d] = lb;
@@ -471,17 +527,20 @@ __device__ __forceinline__ bool forward_part(const KParams<R>& P, const FAcc& ac
   return push_move<DIMS, R>(P, s, f.Ep, f.Bp, f.sh, f.o1, f.vz, f.small, flg);
 }
 
-// Adjoint of one particle's step from its forward pass; c3 are the cell's
-// coordinates in the accessor's frame.  Reads lam at slot p (adjoints of
-// x^{n+1}, u^{n+1/2}) and overwrites it with those of x^n, u^{n-1/2}.
+// Adjoint of one particle's step from its forward pass, as far back as the
+// interpolated fields; c3 are the cell's coordinates in the accessor's frame.
+// Reads lam at slot p (adjoints of x^{n+1}, u^{n+1/2}); gives lX0 (the adjoint
+// of x^n without the gather's part), lu0 (of u^{n-1/2}), lEp and lBp.
 template <int DIMS, int ORDER, typename R, class Acc>
-__device__ __forceinline__ void adjoint_part(const KParams<R>& P, const Acc& ac, const int* c3,
+__device__ __forceinline__ void adjoint_back(const KParams<R>& P, const Acc& ac, const int* c3,
                                              const PState<R>& s0, const PState<R>& s1,
-                                             const FwdPart<R>& f, const DParts<R>& lam, int p) {
+                                             const FwdPart<R>& f, const DParts<R>& lam, int p,
+                                             R* lX0, R* lu0, R* lEp, R* lBp) {
   const R u1[3] = {s1.u[0], s1.u[1], s1.u[2]};
   const R gam = sqrt(R(1) + u1[0] * u1[0] + u1[1] * u1[1] + u1[2] * u1[2]);
   // adjoints arriving from step n+1
-  R lX1[3] = {R(0), R(0), R(0)}, lX0[3] = {R(0), R(0), R(0)}, lu1[3];
+  R lX1[3] = {R(0), R(0), R(0)}, lu1[3];
+  lX0[0] = lX0[1] = lX0[2] = R(0);
 #pragma unroll
   for (int d = 0; d < DIMS; ++d) lX1[d] = lam.off[d][p];
 #pragma unroll
@@ -503,9 +562,16 @@ __device__ __forceinline__ void adjoint_part(const KParams<R>& P, const Acc& ac,
 #pragma unroll
   for (int c = 0; c < 3; ++c) lu1[c] += (ld[c] + (c == 2 ? lvz : R(0))) * ig - u1[c] * ig3 * dot;
   // Boris
-  R lu0[3], lEp[3], lBp[3];
   boris_vjp<R>(P.hqm, f.u0, f.Ep, f.Bp, lu1, lu0, lEp, lBp);
-  // gather
+}
+
+// The whole step: overwrites lam at slot p with the adjoints of x^n, u^{n-1/2}.
+template <int DIMS, int ORDER, typename R, class Acc>
+__device__ __forceinline__ void adjoint_part(const KParams<R>& P, const Acc& ac, const int* c3,
+                                             const PState<R>& s0, const PState<R>& s1,
+                                             const FwdPart<R>& f, const DParts<R>& lam, int p) {
+  R lX0[3], lu0[3], lEp[3], lBp[3];
+  adjoint_back<DIMS, ORDER, R>(P, ac, c3, s0, s1, f, lam, p, lX0, lu0, lEp, lBp);
   gather_vjp<DIMS, ORDER, R>(ac, c3, s0.o, lEp, lBp, lX0);
 #pragma unroll
   for (int d = 0; d < DIMS; ++d) lam.off[d][p] = lX0[d];
@@ -544,22 +610,24 @@ __global__ void __launch_bounds__(256) k_push_deposit_adjoint(KParams<R> P, DPar
 }
 
 // The same out of LDS, one workgroup per tile of sorted particles, or per z
-// slab of one in 3D (AdjGeo): E^n, B^n and lamJ of the region are staged,
-// lamE/lamB accumulate in double in LDS and are added to the global arrays
-// once.  Every slab reads all of its tile's particles and takes those whose
-// cell is in the slab, the first and last slabs also the allowance below
-// and above the tile.  Particles outside the tile's drift allowance, or
-// moving half a cell or more, go to the list for the global-memory kernel
-// (entered by the first slab alone).
-template <int DIMS, int ORDER, typename R>
-__global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
-    KParams<R> P, DParts<R> pa, DFields<R> F, DFields<R> L, DParts<R> lam,
-    const int* __restrict__ starts, int* __restrict__ deferred, DevFlags* flg) {
-  using G = AdjGeo<DIMS, ORDER, R>;
+// slab of one (AdjGeo): the phase's regions are staged, lamE/lamB accumulate in
+// double in LDS and are added to the global arrays once.  Every slab reads all
+// of its tile's particles and takes those whose cell is in the slab, the first
+// and last slabs also the allowance below and above the tile.  Particles
+// outside the tile's drift allowance, or moving half a cell or more, go to the
+// list for the global-memory kernel (entered by PDA_ALL or PDA_BACK, which has
+// one slab); PDA_BACK leaves zeros in `lam_eb` (6 arrays of np) for the ones
+// that moved too far or became non-finite, and PDA_GATHER skips zeros.
+template <int DIMS, int ORDER, typename R, int PHASE>
+__global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
+                                  (AdjGeo<DIMS, ORDER, R, PHASE>::WPE)) k_pda_tile(
+    KParams<R> P, DParts<R> pa, DFields<R> F, DFields<R> L, DParts<R> lam, R* __restrict__ lam_eb,
+    long np, const int* __restrict__ starts, int* __restrict__ deferred, DevFlags* flg) {
+  using G = AdjGeo<DIMS, ORDER, R, PHASE>;
   constexpr int S = G::S;
   __shared__ R s_eb[6 * G::e_vol];
-  __shared__ R s_lj[3 * G::j_vol];
-  __shared__ double s_leb[6 * G::e_vol];
+  __shared__ R s_lj[G::has_lj ? 3 * G::j_vol : 1];
+  __shared__ double s_leb[G::has_leb ? 6 * G::e_vol : 1];
   const int grp = blockIdx.x >> 3;
   const int tile = (blockIdx.x & 7) * P.per_xcd + grp / S;
   const int slab = grp % S;
@@ -568,7 +636,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
   if (pbeg == pend) return;
   int org[3];
   tile_origin<DIMS, ORDER, R>(P, tile, org);
-  const int torg2 = org[2];
+  const int tor[3] = {org[0], org[1], org[2]};
   org[2] += slab * G::TZ;
   const int open0 = P.bc[0] == PIC_BC_OPEN, open1 = P.bc[1] == PIC_BC_OPEN;
   const int open2 = DIMS == 3 && P.bc[2] == PIC_BC_OPEN;
@@ -586,77 +654,99 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
       }
     }
   }
-  for (int r = threadIdx.x; r < G::j_vol; r += G::NT) {  // lamJ_c, staggered along c
-    const int lx = r % G::jx, ly = (r / G::jx) % G::jx, lz = r / (G::jx * G::jx);
-    int sx[2], sy[2], sz[2] = {0, 0};
-    axis_slots(org[0] + G::j_lo + lx, P.n[0], open0, 1, sx);
-    axis_slots(org[1] + G::j_lo + ly, P.n[1], open1, str1, sy);
-    if (DIMS == 3) axis_slots(org[2] + G::j_lo_z + lz, P.n[2], open2, str2, sz);
+  if constexpr (G::has_lj) {
+    for (int r = threadIdx.x; r < G::j_vol; r += G::NT) {  // lamJ_c, staggered along c
+      const int lx = r % G::jx, ly = (r / G::jx) % G::jx, lz = r / (G::jx * G::jx);
+      int sx[2], sy[2], sz[2] = {0, 0};
+      axis_slots(org[0] + G::j_lo + lx, P.n[0], open0, 1, sx);
+      axis_slots(org[1] + G::j_lo + ly, P.n[1], open1, str1, sy);
+      if (DIMS == 3) axis_slots(org[2] + G::j_lo_z + lz, P.n[2], open2, str2, sz);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int ix = sx[c == 0], iy = sy[c == 1], iz = sz[c == 2];
-      s_lj[c * G::j_vol + r] = (ix >= 0 && iy >= 0 && iz >= 0) ? L.J[c][ix + iy + iz] : R(0);
+      for (int c = 0; c < 3; ++c) {
+        const int ix = sx[c == 0], iy = sy[c == 1], iz = sz[c == 2];
+        s_lj[c * G::j_vol + r] = (ix >= 0 && iy >= 0 && iz >= 0) ? L.J[c][ix + iy + iz] : R(0);
+      }
     }
   }
-  for (int i = threadIdx.x; i < 6 * G::e_vol; i += G::NT) s_leb[i] = 0.0;
+  if constexpr (G::has_leb)
+    for (int i = threadIdx.x; i < 6 * G::e_vol; i += G::NT) s_leb[i] = 0.0;
   __syncthreads();
-  const AdjLds<DIMS, ORDER, R, G> ac{s_eb, s_lj, s_leb};
+  const AdjLds<DIMS, ORDER, R, G> ac{(lds_ptr<const R>)s_eb, (lds_ptr<const R>)s_lj,
+                                     (lds_ptr<double>)s_leb};
+  // the cell relative to the tile (periodic fold); false outside the tile's
+  // drift allowance
+  auto locate = [&](const int* c3, int* l) {
+    bool fast = true;
+#pragma unroll
+    for (int d = 0; d < DIMS; ++d) {
+      const int Td = d == 2 ? G::B::TZ : G::T;
+      const int Ad = d == 2 ? G::AZ : G::A;
+      int v = c3[d] - tor[d];
+      if (P.bc[d] == PIC_BC_PERIODIC) {
+        v = v < 0 ? v + P.n[d] : v;
+        if (v >= Td + Ad) v -= P.n[d];
+      }
+      l[d] = v;
+      fast = fast && v >= -Ad && v < Td + Ad;
+    }
+    return fast;
+  };
+  auto defer = [&](int p) { deferred[atomicAdd(&flg->ndefer, 1u)] = p; };
+  // one particle whose cell l (relative to the slab) is in the region
+  auto work = [&](int p, const PState<R>& s0, const int* l) {
+    if constexpr (PHASE == PDA_GATHER) {
+      R v[6];
+      bool any = false;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        v[c] = lam_eb[c * np + p];
+        any = any || v[c] != R(0);  // (also for NaN)
+      }
+      if (!any) return;
+      R lX[3] = {R(0), R(0), R(0)};
+      gather_vjp<DIMS, ORDER, R>(ac, l, s0.o, v, v + 3, lX);
+#pragma unroll
+      for (int d = 0; d < DIMS; ++d) lam.off[d][p] += lX[d];
+    } else {
+      const LdsFields<DIMS, ORDER, R, G> acc{
+          (lds_ptr<const R>)s_eb,
+          (l[2] - G::e_lo_z) * G::ep + (l[1] - G::e_lo) * G::es + (l[0] - G::e_lo)};
+      PState<R> s = s0;
+      FwdPart<R> f;
+      bool ok = forward_part<DIMS, ORDER, R>(P, acc, s, f, flg);
+      if (ok && !f.small) {
+        defer(p);
+        ok = false;
+      }
+      if constexpr (PHASE == PDA_ALL) {
+        if (ok) adjoint_part<DIMS, ORDER, R>(P, ac, l, s0, s, f, lam, p);
+      } else {
+        R lX0[3], lu0[3], v[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
+        if (ok) {
+          adjoint_back<DIMS, ORDER, R>(P, ac, l, s0, s, f, lam, p, lX0, lu0, v, v + 3);
+#pragma unroll
+          for (int d = 0; d < DIMS; ++d) lam.off[d][p] = lX0[d];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) lam.u[c][p] = lu0[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) lam_eb[c * np + p] = v[c];
+      }
+    }
+  };
   if constexpr (S == 1) {
     for (int p = pbeg + threadIdx.x; p < pend; p += G::NT) {
-      PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
+      const PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
       if (s.cl < 0) continue;
-      int c3[3] = {0, 0, 0};
+      int c3[3] = {0, 0, 0}, l[3] = {0, 0, 0};
       if (!decode<DIMS, R>(P, s, c3, flg)) continue;
-      const int tor[3] = {org[0], org[1], torg2};
-      int l[3] = {0, 0, 0};
-      bool fast = true;
-#pragma unroll
-      for (int d = 0; d < DIMS; ++d) {
-        const int Td = d == 2 ? G::B::TZ : G::T;
-        const int Ad = d == 2 ? G::AZ : G::A;
-        int v = c3[d] - tor[d];
-        if (P.bc[d] == PIC_BC_PERIODIC) {
-          v = v < 0 ? v + P.n[d] : v;
-          if (v >= Td + Ad) v -= P.n[d];
-        }
-        l[d] = v;
-        fast = fast && v >= -Ad && v < Td + Ad;
-      }
-      if (!fast) {
-        if (slab == 0) deferred[atomicAdd(&flg->ndefer, 1u)] = p;
-        continue;
-      }
-      LdsFields<DIMS, ORDER, R, G> acc{
-          (lds_ptr<const R>)s_eb, ((l[2] - G::e_lo_z) * G::ex + (l[1] - G::e_lo)) * G::ex + (l[0] - G::e_lo)};
-      const PState<R> s0 = s;
-      FwdPart<R> f;
-      if (!forward_part<DIMS, ORDER, R>(P, acc, s, f, flg)) continue;
-      if (!f.small) {
-        deferred[atomicAdd(&flg->ndefer, 1u)] = p;
-        continue;
-      }
-      adjoint_part<DIMS, ORDER, R>(P, ac, l, s0, s, f, lam, p);
+      if (locate(c3, l))
+        work(p, s, l);
+      else if (PHASE != PDA_GATHER)
+        defer(p);
     }
   } else {
-    const int tor[3] = {org[0], org[1], torg2};
-    // the cell relative to the tile (periodic fold); false outside the
-    // tile's drift allowance
-    auto locate = [&](const int* c3, int* l) {
-      bool fast = true;
-#pragma unroll
-      for (int d = 0; d < DIMS; ++d) {
-        const int Td = d == 2 ? G::B::TZ : G::T;
-        const int Ad = d == 2 ? G::AZ : G::A;
-        int v = c3[d] - tor[d];
-        if (P.bc[d] == PIC_BC_PERIODIC) {
-          v = v < 0 ? v + P.n[d] : v;
-          if (v >= Td + Ad) v -= P.n[d];
-        }
-        l[d] = v;
-        fast = fast && v >= -Ad && v < Td + Ad;
-      }
-      return fast;
-    };
+    static_assert(S == 1 || PHASE == PDA_GATHER, "particles are deferred once");
     // Every slab scans all of the tile's particles, a slab's share is about
     // 1/S of them: each wavefront queues the indices of its slab's particles
     // (allowance cells below and above the tile go to the end slabs) and
@@ -673,15 +763,9 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
         bool own = false;
         if (p < pend) {
           const PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
-          int c3[3] = {0, 0, 0};
-          if (s.cl >= 0 && decode<DIMS, R>(P, s, c3, flg)) {
-            int l[3] = {0, 0, 0};
-            if (!locate(c3, l)) {
-              if (slab == 0) deferred[atomicAdd(&flg->ndefer, 1u)] = p;
-            } else {
-              own = (l[2] < 0 ? 0 : (l[2] / G::TZ < S ? l[2] / G::TZ : S - 1)) == slab;
-            }
-          }
+          int c3[3] = {0, 0, 0}, l[3] = {0, 0, 0};
+          if (s.cl >= 0 && decode<DIMS, R>(P, s, c3, flg) && locate(c3, l))
+            own = (l[2] < 0 ? 0 : (l[2] / G::TZ < S ? l[2] / G::TZ : S - 1)) == slab;
         }
         const unsigned long long m = __ballot(own);
         if (own) q[qn + (int)__popcll(m & ((1ull << lane) - 1ull))] = p;
@@ -694,28 +778,18 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
         __builtin_amdgcn_wave_barrier();
         qn -= cnt;
         if (p >= 0) {
-          PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
-          int c3[3] = {0, 0, 0};
+          const PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
+          int c3[3] = {0, 0, 0}, l[3] = {0, 0, 0};
           decode<DIMS, R>(P, s, c3, flg);
-          int l[3] = {0, 0, 0};
           locate(c3, l);
           l[2] -= slab * G::TZ;
-          LdsFields<DIMS, ORDER, R, G> acc{(lds_ptr<const R>)s_eb,
-                                           ((l[2] - G::e_lo_z) * G::ex + (l[1] - G::e_lo)) * G::ex +
-                                               (l[0] - G::e_lo)};
-          const PState<R> s0 = s;
-          FwdPart<R> f;
-          if (forward_part<DIMS, ORDER, R>(P, acc, s, f, flg)) {
-            if (!f.small)
-              deferred[atomicAdd(&flg->ndefer, 1u)] = p;
-            else
-              adjoint_part<DIMS, ORDER, R>(P, ac, l, s0, s, f, lam, p);
-          }
+          work(p, s, l);
         }
       }
       if (!more) break;
     }
   }
+  if constexpr (!G::has_leb) return;
   __syncthreads();
   // lamE, lamB of the region (its halo overlaps the neighbouring regions')
   for (int r = threadIdx.x; r < G::e_vol; r += G::NT) {
@@ -731,7 +805,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R>::NT)) k_pda_tile(
       const int ix = sx[isb ? (e != 0) : (e == 0)];
       const int iy = sy[isb ? (e != 1) : (e == 1)];
       const int iz = sz[isb ? (e != 2) : (e == 2)];
-      const double v = s_leb[c * G::e_vol + r];
+      const double v = G::has_leb ? s_leb[c * G::e_vol + r] : 0.0;
       if (v != 0.0 && ix >= 0 && iy >= 0 && iz >= 0) atomicAdd(&(isb ? L.B : L.E)[e][ix + iy + iz], (R)v);
     }
   }
@@ -774,18 +848,26 @@ static int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fiel
   // workspace (any particle order is then handled correctly: a particle
   // outside the allowance of the tile whose range holds it takes the
   // global-memory kernel)
-  if constexpr (AdjGeo<DIMS, ORDER, R>::fits) {
-    if (ctx->sorted_np == p->np && ctx->sorted_ws == ws) {
-      using G = AdjGeo<DIMS, ORDER, R>;
-      const int* starts = (const int*)((char*)ws + Lw.starts);
-      int* deferred = (int*)((char*)ws + Lw.tmp_cell);
-      k_adj_reset<<<dim3(1), dim3(1), 0, s>>>(flg);
-      k_pda_tile<DIMS, ORDER, R><<<dim3(8 * P.per_xcd * G::S), dim3(G::NT), 0, s>>>(P, pa, F, L, la,
-                                                                            starts, deferred, flg);
-      k_push_deposit_adjoint<DIMS, ORDER, R><<<dim3(gblocks), dim3(256), 0, s>>>(
-          P, pa, F, L, la, flg, (int)p->np, deferred, starts + P.ntiles);
-      return (int)hipGetLastError();
+  if (ctx->sorted_np == p->np && ctx->sorted_ws == ws) {
+    const int* starts = (const int*)((char*)ws + Lw.starts);
+    int* deferred = (int*)((char*)ws + Lw.tmp_cell);
+    R* lam_eb = (R*)((char*)ws + Lw.tmp_real);  // (the sort's scratch, free here)
+    k_adj_reset<<<dim3(1), dim3(1), 0, s>>>(flg);
+    auto phase = [&](auto ph) {
+      constexpr int PH = decltype(ph)::value;
+      using G = AdjGeo<DIMS, ORDER, R, PH>;
+      k_pda_tile<DIMS, ORDER, R, PH><<<dim3(8 * P.per_xcd * G::S), dim3(G::NT), 0, s>>>(
+          P, pa, F, L, la, lam_eb, (long)p->np, starts, deferred, flg);
+    };
+    if constexpr (DIMS == 2) {
+      phase(std::integral_constant<int, PDA_ALL>{});
+    } else {
+      phase(std::integral_constant<int, PDA_BACK>{});
+      phase(std::integral_constant<int, PDA_GATHER>{});
     }
+    k_push_deposit_adjoint<DIMS, ORDER, R><<<dim3(gblocks), dim3(256), 0, s>>>(
+        P, pa, F, L, la, flg, (int)p->np, deferred, starts + P.ntiles);
+    return (int)hipGetLastError();
   }
   k_push_deposit_adjoint<DIMS, ORDER, R><<<dim3(gblocks), dim3(256), 0, s>>>(
       P, pa, F, L, la, flg, (int)p->np, nullptr, nullptr);
