@@ -234,31 +234,6 @@ __global__ void __launch_bounds__(256) k_advance_e(
   }
 }
 
-// Tangential E on the boundary plane of an open axis d != c?  Returns the
-// number of such axes and the lowest one.
-__device__ __forceinline__ int mur_axes(const FdParams& P, int c, int i, int j, int k, int& lowest) {
-  const int L[3] = {i, j, k};
-  int cnt = 0;
-  lowest = -1;
-  for (int d = 0; d < P.dims; ++d) {
-    if (d == c || !P.open[d]) continue;
-    if (L[d] == 0 || L[d] == P.n[d] - 1) {
-      if (cnt == 0) lowest = d;
-      ++cnt;
-    }
-  }
-  return cnt;
-}
-
-template <typename R>
-__global__ void k_fill3_zero(R* a, R* b, R* c, long n) {
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    a[i] = R(0);
-    b[i] = R(0);
-    c[i] = R(0);
-  }
-}
-
 static FdParams fd_params(const pic_config& cf, bool& any_open) {
   FdParams P;
   P.dims = cf.dims;
@@ -328,165 +303,189 @@ int launch_field_advance(const pic_ctx* ctx, const pic_fields* f, hipStream_t s)
 // Transpose of the field advance (for the hand-written adjoint of the step).
 // The advance is linear in (E, B, J); with mu the adjoint of E^{n+1} after
 // the last half step, its transpose is, in reverse order:
-//   lamE -= h C^T mask(lamB)                      (the last half step)
-//   Mur updates transposed, edge pass then face pass
-//   lamB += dt C mu_interior;  lamJ = -dt mu_interior
+//   mu = lamE - h C^T mask(lamB)                  (the last half step)
+//   Mur updates transposed, edges then faces
+//   lamJ = -dt mu on the samples the Yee update advances, 0 elsewhere
+//   lamB += dt C mu_interior = -C lamJ
 //   lamE = mu (+ the direct F1^n terms of Mur);   lamE -= h C^T mask(lamB)
 // where mask() keeps the B samples inside the domain (the only ones the
-// forward updates or reads) and mu_interior keeps the E samples advanced by
-// the Yee update.
+// forward updates or reads).  Three passes: k_adj_e_mur (the first three
+// lines, and the F1^n terms), k_adj_b, k_adj_e.  The middle pass reads mu from
+// lamJ, which is zero exactly where the forward does not advance, so that
+// lamE can already hold the sum with the Mur terms and no array is kept
+// beside them (512x256, open y, FP32: 9 launches of about 4.5 us before, now 3;
+// a rollout of 10 steps forward and back 4.00 -> 3.80 ms).
 
-// lamE -= h C^T lamB over every E sample, lamB read only inside the domain.
-template <typename R>
-__global__ void k_adj_curl_b(FdParams P, R* __restrict__ L0, R* __restrict__ L1, R* __restrict__ L2,
-                             const R* __restrict__ B0, const R* __restrict__ B1,
-                             const R* __restrict__ B2, R gx, R gy, R gz, int ncell) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// h C^T lamB at one sample: component c, (i, j, k), lamB read only inside the
+// domain.
+template <typename R, int DIMS, bool OPEN>
+struct AdjCurlB {
+  const FdParams& P;
+  const R* B[3];
+  R h[3];
+  __device__ __forceinline__ R value(int comp, int i, int j, int k) const {
+    if (OPEN && !inside(P, i, j, k, comp != 0, comp != 1, comp != 2)) return R(0);
+    return B[comp][i + P.n[0] * (j + P.n[1] * k)];
+  }
+  // value one sample lower along axis d (0 beyond an open face)
+  __device__ __forceinline__ R lower(int comp, int i, int j, int k, int d) const {
+    int L[3] = {i, j, k};
+    L[d] -= 1;
+    if (L[d] < 0) {
+      if (OPEN && P.open[d]) return R(0);
+      L[d] += P.n[d];
+    }
+    return value(comp, L[0], L[1], L[2]);
+  }
+  __device__ __forceinline__ R operator()(int c, int i, int j, int k) const {
+    const int a = (c + 1) % 3, b = (c + 2) % 3;
+    R curl = R(0);
+    if (a < DIMS) curl += h[a] * (value(b, i, j, k) - lower(b, i, j, k, a));
+    if (b < DIMS) curl -= h[b] * (value(a, i, j, k) - lower(a, i, j, k, b));
+    return curl;
+  }
+};
+
+// mu, lamJ and the Mur terms of one cell.  The forward's Mur update of a face
+// sample F0 <- F1^n + kappa (F1 - F0^n) transposes to mu1 += kappa mu0,
+// x1 += mu0, mu0 <- -kappa mu0 (x: the direct terms, summed into lamE): the
+// thread of the inner neighbour does it, for its face samples along the two
+// axes a < b other than the component's and, first, the edge both meet in
+// (which the forward takes from the face sample along b).  Face samples are
+// otherwise untouched here: their own threads skip them.
+template <typename R, int DIMS, bool OPEN>
+__global__ void __launch_bounds__(256) k_adj_e_mur(FdParams P, R* __restrict__ L0,
+                                                   R* __restrict__ L1, R* __restrict__ L2,
+                                                   const R* __restrict__ B0,
+                                                   const R* __restrict__ B1,
+                                                   const R* __restrict__ B2, R* __restrict__ J0,
+                                                   R* __restrict__ J1, R* __restrict__ J2, R hx,
+                                                   R hy, R hz, R kx, R ky, R kz, R dt, int ncell) {
+  const int idx = xcd_block() * blockDim.x + threadIdx.x;
   if (idx >= ncell) return;
   int i, j, k;
   decompose(P, idx, i, j, k);
   R* Lm[3] = {L0, L1, L2};
-  const R* B[3] = {B0, B1, B2};
-  const R g[3] = {gx, gy, gz};  // h / dx_d
-  auto bval = [&](int comp, int ii, int jj, int kk, int d, int step) -> R {
-    int Lc[3] = {ii, jj, kk};
-    Lc[d] += step;
-    if (Lc[d] < 0 || Lc[d] >= P.n[d]) {
-      if (P.open[d]) return R(0);
-      Lc[d] = Lc[d] < 0 ? Lc[d] + P.n[d] : Lc[d] - P.n[d];
-    }
-    if (!inside(P, Lc[0], Lc[1], Lc[2], comp != 0, comp != 1, comp != 2)) return R(0);
-    return B[comp][Lc[0] + P.n[0] * (Lc[1] + P.n[1] * Lc[2])];
-  };
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const int a = (c + 1) % 3, b = (c + 2) % 3;
-    R curl = R(0);
-    if (a < P.dims) curl += g[a] * (bval(b, i, j, k, a, 0) - bval(b, i, j, k, a, -1));
-    if (b < P.dims) curl -= g[b] * (bval(a, i, j, k, b, 0) - bval(a, i, j, k, b, -1));
-    Lm[c][idx] -= curl;
-  }
-}
-
-// Mur transpose for the samples of face (d, side) with `pass` open
-// boundary axes: mu[s1] += kappa mu[s0]; extra[s1] += mu[s0]; the sample's
-// own adjoint becomes -kappa mu[s0] (+ what it received as a neighbour,
-// kept in extra).  Runs for pass 2, then pass 1.
-template <typename R>
-__global__ void k_adj_mur(FdParams P, R* __restrict__ M0, R* __restrict__ M1, R* __restrict__ M2,
-                          R* __restrict__ X0, R* __restrict__ X1, R* __restrict__ X2, int d,
-                          int side, int pass, R kappa) {
-  const int a = d == 0 ? 1 : 0, b = d == 2 ? 1 : 2;
-  const int na = P.n[a], nbv = b < P.dims ? P.n[b] : 1;
-  const long plane = (long)na * nbv;
-  const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if (t >= 2 * plane) return;
-  const int which = (int)(t / plane);
-  const long r = t - which * plane;
-  const int c = (d + 1 + which) % 3;
-  int L[3];
-  L[d] = side ? P.n[d] - 1 : 0;
-  L[a] = (int)(r % na);
-  L[b] = (int)(r / na);
-  if (!inside(P, L[0], L[1], L[2], c == 0, c == 1, c == 2)) return;
-  int lowest;
-  if (mur_axes(P, c, L[0], L[1], L[2], lowest) != pass || lowest != d) return;
-  R* M[3] = {M0, M1, M2};
-  R* X[3] = {X0, X1, X2};
-  const int i0 = L[0] + P.n[0] * (L[1] + P.n[1] * L[2]);
-  int N[3] = {L[0], L[1], L[2]};
-  N[d] += side ? -1 : 1;
-  const int i1 = N[0] + P.n[0] * (N[1] + P.n[1] * N[2]);
-  const R mu0 = M[c][i0];
-  M[c][i1] += kappa * mu0;
-  X[c][i1] += mu0;
-  M[c][i0] = -kappa * mu0 + X[c][i0];
-  X[c][i0] = R(0);
-}
-
-// lamB += dt C mu over the inside B samples, mu read on the E samples the
-// Yee update advances (interior ones).
-template <typename R>
-__global__ void k_adj_curl_e(FdParams P, const R* __restrict__ M0, const R* __restrict__ M1,
-                             const R* __restrict__ M2, R* __restrict__ B0, R* __restrict__ B1,
-                             R* __restrict__ B2, R gx, R gy, R gz, int ncell) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= ncell) return;
-  int i, j, k;
-  decompose(P, idx, i, j, k);
-  const R* M[3] = {M0, M1, M2};
-  R* B[3] = {B0, B1, B2};
-  const R g[3] = {gx, gy, gz};  // dt / dx_d
-  auto muval = [&](int comp, int ii, int jj, int kk, int d, int step) -> R {
-    int Lc[3] = {ii, jj, kk};
-    Lc[d] += step;
-    if (Lc[d] < 0 || Lc[d] >= P.n[d]) {
-      if (P.open[d]) return R(0);
-      Lc[d] = Lc[d] < 0 ? Lc[d] + P.n[d] : Lc[d] - P.n[d];
-    }
-    if (!inside(P, Lc[0], Lc[1], Lc[2], comp == 0, comp == 1, comp == 2)) return R(0);
-    int lowest;
-    if (mur_axes(P, comp, Lc[0], Lc[1], Lc[2], lowest) > 0) return R(0);
-    return M[comp][Lc[0] + P.n[0] * (Lc[1] + P.n[1] * Lc[2])];
-  };
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (!inside(P, i, j, k, c != 0, c != 1, c != 2)) continue;
-    const int a = (c + 1) % 3, b = (c + 2) % 3;
-    R acc = R(0);
-    if (a < P.dims) acc += g[a] * (muval(b, i, j, k, a, 1) - muval(b, i, j, k, a, 0));
-    if (b < P.dims) acc -= g[b] * (muval(a, i, j, k, b, 1) - muval(a, i, j, k, b, 0));
-    B[c][idx] += acc;
-  }
-}
-
-// lamJ = -dt mu on interior E samples (0 elsewhere); lamE = mu + extra there.
-template <typename R>
-__global__ void k_adj_e_out(FdParams P, R* __restrict__ M0, R* __restrict__ M1, R* __restrict__ M2,
-                            R* __restrict__ J0, R* __restrict__ J1, R* __restrict__ J2,
-                            R* __restrict__ X0, R* __restrict__ X1, R* __restrict__ X2, R dt,
-                            int ncell, int has_extra) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= ncell) return;
-  int i, j, k;
-  decompose(P, idx, i, j, k);
-  R* M[3] = {M0, M1, M2};
   R* J[3] = {J0, J1, J2};
-  R* X[3] = {X0, X1, X2};
+  const AdjCurlB<R, DIMS, OPEN> curl{P, {B0, B1, B2}, {hx, hy, hz}};
+  const int L[3] = {i, j, k};
+  const int str[3] = {1, P.n[0], P.n[0] * P.n[1]};
+  const R kap[3] = {kx, ky, kz};
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    int lowest;
-    const bool yee = inside(P, i, j, k, c == 0, c == 1, c == 2) && mur_axes(P, c, i, j, k, lowest) == 0;
-    if (yee) {
-      J[c][idx] = -dt * M[c][idx];
-      if (has_extra) {
-        M[c][idx] += X[c][idx];
-        X[c][idx] = R(0);
+    const int a = c == 0 ? 1 : 0, b = c == 2 ? 1 : 2;  // the other axes, a < b
+    const bool in = !OPEN || inside(P, i, j, k, c == 0, c == 1, c == 2);
+    bool face = false;
+    int sa = 0, sb = 0;  // the open face one sample away along a, b
+    if (OPEN) {
+      if (P.open[a]) {
+        face = face || L[a] == 0 || L[a] == P.n[a] - 1;
+        sa = L[a] == 1 ? -1 : L[a] == P.n[a] - 2 ? 1 : 0;
       }
-    } else {
-      J[c][idx] = R(0);
+      if (b < DIMS && P.open[b]) {
+        face = face || L[b] == 0 || L[b] == P.n[b] - 1;
+        sb = L[b] == 1 ? -1 : L[b] == P.n[b] - 2 ? 1 : 0;
+      }
     }
+    if (!in) {  // outside: only the transposed curl, no advance
+      Lm[c][idx] -= curl(c, i, j, k);
+      J[c][idx] = R(0);
+      continue;
+    }
+    if (face) {
+      J[c][idx] = R(0);
+      continue;
+    }
+    R mu = Lm[c][idx] - curl(c, i, j, k), x = R(0);
+    if (OPEN && (sa | sb)) {
+      auto mu_at = [&](int da, int db) {
+        int M[3] = {i, j, k};
+        M[a] += da;
+        M[b] += db;
+        return Lm[c][idx + da * str[a] + db * str[b]] - curl(c, M[0], M[1], M[2]);
+      };
+      R xb = R(0), mub = R(0);
+      if (sb) mub = mu_at(0, sb);
+      if (sa && sb) {  // the edge, taken from the face sample along b
+        const R e = mu_at(sa, sb);
+        mub += kap[a] * e;
+        xb = e;
+        Lm[c][idx + sa * str[a] + sb * str[b]] = -kap[a] * e;
+      }
+      if (sa) {
+        const R f = mu_at(sa, 0);
+        mu += kap[a] * f;
+        x += f;
+        Lm[c][idx + sa * str[a]] = -kap[a] * f;
+      }
+      if (sb) {
+        mu += kap[b] * mub;
+        x += mub;
+        Lm[c][idx + sb * str[b]] = -kap[b] * mub + xb;
+      }
+    }
+    J[c][idx] = -dt * mu;
+    Lm[c][idx] = mu + x;
   }
 }
 
-template <typename R>
-static int launch_fa_adj(const pic_ctx* ctx, const pic_fields* lam, void* ws, hipStream_t s) {
-  const pic_config& cf = ctx->cfg;
-  FdParams P;
-  P.dims = cf.dims;
-  bool any_open = false;
-  for (int d = 0; d < 3; ++d) {
-    P.n[d] = d < cf.dims ? cf.n[d] : 1;
-    P.open[d] = d < cf.dims && cf.bc[d] == PIC_BC_OPEN;
-    any_open = any_open || P.open[d];
+// lamB -= C lamJ on the inside B samples (forward differences; lamJ = -dt mu
+// on the samples the forward advances, 0 on the others).
+template <typename R, int DIMS, bool OPEN>
+__global__ void __launch_bounds__(256) k_adj_b(FdParams P, const R* __restrict__ J0,
+                                               const R* __restrict__ J1, const R* __restrict__ J2,
+                                               R* __restrict__ B0, R* __restrict__ B1,
+                                               R* __restrict__ B2, R gx, R gy, R gz, int ncell) {
+  const int idx = xcd_block() * blockDim.x + threadIdx.x;
+  if (idx >= ncell) return;
+  int i, j, k;
+  decompose(P, idx, i, j, k);
+  const R* J[3] = {J0, J1, J2};
+  R* B[3] = {B0, B1, B2};
+  const R g[3] = {gx, gy, gz};  // 1 / dx_d
+  const int L[3] = {i, j, k};
+  const int str[3] = {1, P.n[0], P.n[0] * P.n[1]};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (OPEN && !inside(P, i, j, k, c != 0, c != 1, c != 2)) continue;
+    const int a = (c + 1) % 3, b = (c + 2) % 3;
+    // inside along an open axis means a neighbour: only periodic axes wrap
+    auto diff = [&](int v, int d) {
+      const int up = L[d] + 1 < P.n[d] ? str[d] : str[d] - P.n[d] * str[d];
+      return J[v][idx + up] - J[v][idx];
+    };
+    R acc = R(0);
+    if (a < DIMS) acc += g[a] * diff(b, a);
+    if (b < DIMS) acc -= g[b] * diff(a, b);
+    B[c][idx] -= acc;
   }
-  P.dn0.init((uint32_t)P.n[0]);
-  P.dn1.init((uint32_t)P.n[1]);
-  const int ncell = P.n[0] * P.n[1] * P.n[2];
-  R h[3], g[3];
+}
+
+// lamE -= h C^T lamB over every E sample, lamB read only inside the domain.
+template <typename R, int DIMS, bool OPEN>
+__global__ void __launch_bounds__(256) k_adj_e(FdParams P, R* __restrict__ L0, R* __restrict__ L1,
+                                               R* __restrict__ L2, const R* __restrict__ B0,
+                                               const R* __restrict__ B1, const R* __restrict__ B2,
+                                               R hx, R hy, R hz, int ncell) {
+  const int idx = xcd_block() * blockDim.x + threadIdx.x;
+  if (idx >= ncell) return;
+  int i, j, k;
+  decompose(P, idx, i, j, k);
+  R* Lm[3] = {L0, L1, L2};
+  const AdjCurlB<R, DIMS, OPEN> curl{P, {B0, B1, B2}, {hx, hy, hz}};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) Lm[c][idx] -= curl(c, i, j, k);
+}
+
+template <typename R, int DIMS, bool OPEN>
+static int launch_fa_adj_t(const pic_ctx* ctx, const FdParams& P, const pic_fields* lam,
+                           hipStream_t s) {
+  const pic_config& cf = ctx->cfg;
+  R h[3], g[3], kp[3];
   for (int d = 0; d < 3; ++d) {
     h[d] = (R)(0.5 * cf.dt / cf.dx[d]);
-    g[d] = (R)(cf.dt / cf.dx[d]);
+    g[d] = (R)(1.0 / cf.dx[d]);
+    kp[d] = (R)((cf.dt - cf.dx[d]) / (cf.dt + cf.dx[d]));
   }
   R* E[3];
   R* B[3];
@@ -496,48 +495,32 @@ static int launch_fa_adj(const pic_ctx* ctx, const pic_fields* lam, void* ws, hi
     B[c] = (R*)lam->B[c];
     J[c] = (R*)lam->J[c];
   }
-  WsLayout L = ws_layout(ctx, 0);
-  R* extra = (R*)((char*)ws + L.adj);
-  R* X[3] = {extra, extra + ncell, extra + 2 * (long)ncell};
-  const unsigned grid = (unsigned)((ncell + 255) / 256);
-  k_adj_curl_b<R><<<dim3(grid), dim3(256), 0, s>>>(P, E[0], E[1], E[2], B[0], B[1], B[2], h[0],
-                                                  h[1], h[2], ncell);
-  if (any_open) {
-    k_fill3_zero<R><<<dim3(grid < 4096 ? grid : 4096), dim3(256), 0, s>>>(X[0], X[1], X[2], ncell);
-    for (int pass = 2; pass >= 1; --pass)
-      for (int d = 0; d < cf.dims; ++d) {
-        if (!P.open[d]) continue;
-        const int a = d == 0 ? 1 : 0, b = d == 2 ? 1 : 2;
-        const long plane = (long)P.n[a] * P.n[b];
-        const R kappa = (R)((cf.dt - cf.dx[d]) / (cf.dt + cf.dx[d]));
-        for (int sd = 0; sd < 2; ++sd)
-          k_adj_mur<R><<<dim3((unsigned)((2 * plane + 255) / 256)), dim3(256), 0, s>>>(
-              P, E[0], E[1], E[2], X[0], X[1], X[2], d, sd, pass, kappa);
-      }
-  }
-  k_adj_curl_e<R><<<dim3(grid), dim3(256), 0, s>>>(P, E[0], E[1], E[2], B[0], B[1], B[2], g[0],
-                                                  g[1], g[2], ncell);
-  k_adj_e_out<R><<<dim3(grid), dim3(256), 0, s>>>(P, E[0], E[1], E[2], J[0], J[1], J[2], X[0],
-                                                 X[1], X[2], (R)cf.dt, ncell, any_open ? 1 : 0);
-  k_adj_curl_b<R><<<dim3(grid), dim3(256), 0, s>>>(P, E[0], E[1], E[2], B[0], B[1], B[2], h[0],
-                                                  h[1], h[2], ncell);
+  const int ncell = P.n[0] * P.n[1] * P.n[2];
+  const dim3 grid(xcd_grid(ncell)), block(256);
+  k_adj_e_mur<R, DIMS, OPEN><<<grid, block, 0, s>>>(P, E[0], E[1], E[2], B[0], B[1], B[2], J[0],
+                                                    J[1], J[2], h[0], h[1], h[2], kp[0], kp[1],
+                                                    kp[2], (R)cf.dt, ncell);
+  k_adj_b<R, DIMS, OPEN><<<grid, block, 0, s>>>(P, J[0], J[1], J[2], B[0], B[1], B[2], g[0], g[1],
+                                                g[2], ncell);
+  k_adj_e<R, DIMS, OPEN><<<grid, block, 0, s>>>(P, E[0], E[1], E[2], B[0], B[1], B[2], h[0], h[1],
+                                                h[2], ncell);
   return (int)hipGetLastError();
 }
 
-int launch_field_advance_adjoint(const pic_ctx* ctx, const pic_fields* lam, void* ws, hipStream_t s) {
-  return ctx->cfg.real_bytes == 8 ? launch_fa_adj<double>(ctx, lam, ws, s)
-                                  : launch_fa_adj<float>(ctx, lam, ws, s);
+template <typename R>
+static int launch_fa_adj(const pic_ctx* ctx, const pic_fields* lam, hipStream_t s) {
+  bool open;
+  const FdParams P = fd_params(ctx->cfg, open);
+  if (P.dims == 2)
+    return open ? launch_fa_adj_t<R, 2, true>(ctx, P, lam, s)
+                : launch_fa_adj_t<R, 2, false>(ctx, P, lam, s);
+  return open ? launch_fa_adj_t<R, 3, true>(ctx, P, lam, s)
+              : launch_fa_adj_t<R, 3, false>(ctx, P, lam, s);
 }
 
-// Size (in reals) of the adjoint's scratch (open axes only).
-long adj_len(const pic_config& cf) {
-  bool open = false;
-  long ncell = 1;
-  for (int d = 0; d < cf.dims; ++d) {
-    open = open || cf.bc[d] == PIC_BC_OPEN;
-    ncell *= cf.n[d];
-  }
-  return open ? 3 * ncell : 0;
+int launch_field_advance_adjoint(const pic_ctx* ctx, const pic_fields* lam, hipStream_t s) {
+  return ctx->cfg.real_bytes == 8 ? launch_fa_adj<double>(ctx, lam, s)
+                                  : launch_fa_adj<float>(ctx, lam, s);
 }
 
 }  // namespace pic

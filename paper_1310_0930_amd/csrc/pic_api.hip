@@ -12,7 +12,6 @@
 
 namespace pic {
 long diag_len(const pic_config& cf);
-long adj_len(const pic_config& cf);
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -38,9 +37,6 @@ WsLayout ws_layout(const pic_ctx* ctx, int64_t np) {
   L.diag_len = (size_t)diag_len(ctx->cfg);
   L.diag = off;
   off = align256(off + sizeof(double) * L.diag_len);
-  L.adj_len = (size_t)adj_len(ctx->cfg);
-  L.adj = off;
-  off = align256(off + R * L.adj_len);
   const size_t n = np > 0 ? (size_t)np : 0;
   L.tmp_cell = off;
   off = align256(off + sizeof(int) * n);
@@ -473,7 +469,7 @@ int pic_field_advance_adjoint(pic_ctx* ctx, pic_fields* lam, void* ws, void* str
   int v = check_fields(lam, true);
   if (v) return v;
   if ((v = ensure_device(ctx))) return v;
-  return hip_status(launch_field_advance_adjoint(ctx, lam, ws, (hipStream_t)stream));
+  return hip_status(launch_field_advance_adjoint(ctx, lam, (hipStream_t)stream));
 }
 
 int pic_push_deposit_adjoint(pic_ctx* ctx, const pic_particles* state_n, const pic_fields* EB_n,

@@ -54,3 +54,36 @@ def test_field_advance_against_the_oracle(n, bc, rb):
     for f in ("E", "B"):
         r = getattr(ref, f)
         assert np.abs(st[f] - r).max() <= 48 * eps * np.abs(r).max(), f
+
+
+@pytest.mark.parametrize("rb", [8, 4])
+@pytest.mark.parametrize("n,bc", [s for s in SIZES if np.prod(s[0]) < 10000])
+def test_field_advance_transpose_dot_product(n, bc, rb):
+    """<lam, A f> = <A^T lam, f> for the field advance A and random lam, f
+    (zero outside the domain), at the smallest axes, with every edge of open
+    faces.  Either side sums N products of values of at most 6 whose factors
+    carry at most 24 rounded operations each: sqrt(N) 36 48 half-units."""
+    from paper_1310_0930_amd import pic as P
+    from paper_1310_0930_amd.pic import Simulation
+    w = I.Workload("fields", len(n), n, (0.2, 0.25, 0.3)[: len(n)], 2, 1, 0.0, 1, bc=bc)
+    cfg = O.Config(w.dims, w.n3, w.dx3, w.dt, w.order, w.bc3)
+    E, B, J = _random_fields(cfg, sum(n) + rb)
+    lE, lB, _ = _random_fields(cfg, 1000 + sum(n) + rb)
+    sim = Simulation(w.dims, w.n3, w.dx3, w.dt, w.order, rb, w.bc3)
+    sim.load(EMPTY, E, B, with_id=False)
+
+    def put(F):
+        return torch.from_numpy(F.reshape(3, -1)).to(sim.device, sim.real)
+
+    def dot(a, b):
+        return float((a.double() * b.double()).sum())
+
+    sim.J.copy_(put(J))
+    LE, LB, LJ = put(lE), put(lB), torch.full_like(sim.J, float("nan"))  # lamJ is overwritten
+    f0 = [F.clone() for F in (sim.E, sim.B, sim.J)]
+    sim.field_advance()
+    left = dot(LE, sim.E) + dot(LB, sim.B)
+    P.pic_field_advance_adjoint(sim.ctx, P.fields_struct(LE, LB, LJ), sim.ws.data_ptr(), sim.stream)
+    right = dot(LE, f0[0]) + dot(LB, f0[1]) + dot(LJ, f0[2])
+    eps = np.finfo(np.float64 if rb == 8 else np.float32).eps
+    assert abs(left - right) <= np.sqrt(6 * sim.ncell) * 36 * 24 * eps
