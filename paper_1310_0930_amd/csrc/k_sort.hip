@@ -18,10 +18,9 @@
 // layout decays, so the class and cell used for the placement are those a
 // straight-line estimate gives half a sort interval ahead (the particle's
 // tile is still that of its present cell); the layout is then best in the
-// middle of the interval rather than at its start.  The tile-level pass aggregates runs
-// of equal tiles inside a wavefront (particles stay in their tile for many
-// steps), one global atomic per run; the placement runs in LDS, one
-// workgroup per tile.
+// middle of the interval rather than at its start.  The tile-level pass counts
+// a workgroup's particles per tile in an LDS table, one global atomic per tile
+// and workgroup; the placement runs in LDS, one workgroup per tile.
 #include <type_traits>
 
 #include "k_common.h"
@@ -60,22 +59,67 @@ __device__ __forceinline__ int tile_key(const SortParams& S, int cl, int ncell) 
   return (cx >> S.lgT[0]) + S.ntile[0] * ((cy >> S.lgT[1]) + S.ntile[1] * (cz >> S.lgT[2]));
 }
 
-// Run structure of the keys held by one wavefront: a lane starts a run when
-// its key differs from the previous lane's.  Returns the run's first lane and
-// its length (for the first lane).
-template <typename K>
-__device__ __forceinline__ void wave_runs(K key, int& head_lane, int& run_len) {
+// A workgroup's table of the tiles its particles are in (open addressing),
+// with a count per tile: particles of one tile are mostly, but after some steps
+// no longer wholly, next to each other, and runs of equal tiles in a wavefront
+// then are short (a moving window's shift, or ten warm steps, leave about a
+// dozen per wavefront, and an atomic each to a few hundred tile counters took
+// 115 us to count 2.9M particles).
+constexpr int HT = 256, HT_PROBES = 16;
+struct TileTable {
+  int key[HT];
+  int cnt[HT];
+};
+
+__device__ __forceinline__ void table_clear(TileTable& T) {
+  for (int i = threadIdx.x; i < HT; i += blockDim.x) {
+    T.key[i] = -1;
+    T.cnt[i] = 0;
+  }
+}
+
+// Slot of a key, entered if it is new; -1 when none of HT_PROBES slots is its
+// own or free (particles in no order: the caller goes to the global counter).
+__device__ __forceinline__ int table_slot(TileTable& T, int key) {
+  int h = (int)(((unsigned)key * 2654435761u) >> 24);
+  for (int n = 0; n < HT_PROBES; ++n) {
+    int k = T.key[h];
+    if (k == -1) {
+      k = atomicCAS(&T.key[h], -1, key);
+      if (k == -1) k = key;
+    }
+    if (k == key) return h;
+    h = (h + 1) & (HT - 1);
+  }
+  return -1;
+}
+
+// Adds the wavefront's keys (< 0: none) to the table and gives each lane its
+// slot and its rank among the workgroup's particles of that tile.  The lanes
+// that share the first lane's tile, mostly all of them, take one LDS atomic.
+__device__ __forceinline__ void table_rank(TileTable& T, int key, int& slot, int& rank) {
   const int lane = threadIdx.x & 63;
-  const int prev = __shfl_up(key, 1, 64);
-  const bool boundary = lane == 0 || key != prev;
-  const unsigned long long b = __ballot(boundary);
-  // first lane of my run: highest boundary at or below me
-  const unsigned long long below = lane == 63 ? b : (b & ((2ull << lane) - 1));
-  head_lane = 63 - __clzll(below);
-  // next boundary above my run head
-  const unsigned long long above = head_lane == 63 ? 0ull : (b & ~((2ull << head_lane) - 1));
-  const int next = above ? __ffsll(above) - 1 : 64;
-  run_len = next - head_lane;
+  slot = -1;
+  rank = 0;
+  const int lead = __builtin_amdgcn_readfirstlane(key);
+  const unsigned long long same = __ballot(key == lead);
+  if (lead >= 0) {
+    int s0 = 0, r0 = 0;
+    if (lane == 0) {
+      s0 = table_slot(T, lead);
+      if (s0 >= 0) r0 = atomicAdd(&T.cnt[s0], (int)__popcll(same));
+    }
+    s0 = __builtin_amdgcn_readfirstlane(s0);
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    if (key == lead) {
+      slot = s0;
+      rank = r0 + (int)__popcll(same & ((1ull << lane) - 1ull));
+    }
+  }
+  if (key >= 0 && key != lead) {
+    slot = table_slot(T, key);
+    if (slot >= 0) rank = atomicAdd(&T.cnt[slot], 1);
+  }
 }
 
 // Workgroup b of n takes chunk (b * M) mod n (M prime; a permutation of
@@ -88,111 +132,138 @@ __device__ __forceinline__ long spread_block(unsigned b, unsigned n) {
   return n % M == 0 ? (long)b : (long)(((unsigned long long)b * M) % n);
 }
 
-// Tile key of every particle (ntiles: dead) and the histogram of the keys.
-// A workgroup takes COUNT_PER consecutive particles (chunks spread as
-// above); runs of the chunk's first key, which after a sort is the tile of
-// nearly the whole chunk, are summed in LDS and added with one global
-// atomic, other runs add their own.
-constexpr int COUNT_NT = 256, COUNT_PER = 8;
+// Histogram of the particles' tiles (ntiles: dead).  A workgroup takes a chunk
+// of 1024 particles (spread as above), 4 per thread: with 16 a small
+// run has too few wavefronts (a pass with two sorts of a 2D plasma 1063 us
+// against 1032) and a large one gains nothing.
+constexpr int COUNT_NT = 256, COUNT_PER = 4;
 __global__ void __launch_bounds__(COUNT_NT) k_sort_count(SortParams S, const int* __restrict__ cell,
-                                                         long np, int ncell, int* __restrict__ keys,
+                                                         long np, int ncell,
                                                          int* __restrict__ counts, DevFlags* flg) {
-  __shared__ int acc;
+  __shared__ TileTable T;
   const long c0 = spread_block(blockIdx.x, gridDim.x) * (long)(COUNT_NT * COUNT_PER);
   if (c0 == 0 && threadIdx.x == 0) {
     flg->qmax = 0u;  // the scatter takes the new maximum
     flg->ndefer = 0u;  // a new sort interval starts
     flg->since_sort = 0ull;
   }
-  const int lane = threadIdx.x & 63;
-  const int key0 = c0 < np ? tile_key(S, cell[c0], ncell) : -1;
-  if (threadIdx.x == 0) acc = 0;
-  __syncthreads();
-  int mine = 0;  // this thread's run lengths of key0
+  int cl[COUNT_PER];
 #pragma unroll
   for (int k = 0; k < COUNT_PER; ++k) {
     const long p = c0 + k * COUNT_NT + threadIdx.x;
-    const int key = p < np ? tile_key(S, cell[p], ncell) : -1;
-    if (p < np) keys[p] = key;
-    if (__ballot(key == key0) == ~0ull) {  // the whole wavefront in key0's tile (the usual case)
-      if (lane == 0) mine += 64;
-      continue;
-    }
-    int head, len;
-    wave_runs(key, head, len);
-    if (lane == head && key >= 0) {
-      if (key == key0)
-        mine += len;
-      else
-        atomicAdd(&counts[key], len);
-    }
+    cl[k] = p < np ? cell[p] : 0;
   }
-  if (mine) atomicAdd(&acc, mine);
+  table_clear(T);
   __syncthreads();
-  if (threadIdx.x == 0 && acc) atomicAdd(&counts[key0], acc);
-}
-
-// Exclusive scan of counts[0..nb) in three passes: per-block sums, a scan of
-// the block sums (one workgroup), and per-block scans with their offsets.
-// starts[i] = cursor[i] = sum of counts[0..i); starts[nb] = total.
-constexpr int SCAN_B = 1024;
-
-__device__ __forceinline__ int block_incl_scan(int v, int* sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < SCAN_B; off <<= 1) {
-    const int a = t >= off ? sh[t - off] : 0;
-    __syncthreads();
-    sh[t] += a;
-    __syncthreads();
+#pragma unroll
+  for (int k = 0; k < COUNT_PER; ++k) {
+    const long p = c0 + k * COUNT_NT + threadIdx.x;
+    const int key = p < np ? tile_key(S, cl[k], ncell) : -1;
+    int slot, rank;
+    table_rank(T, key, slot, rank);
+    if (key >= 0 && slot < 0) atomicAdd(&counts[key], 1);  // (no slot)
   }
-  return sh[t];
+  __syncthreads();
+  for (int i = threadIdx.x; i < HT; i += COUNT_NT)
+    if (T.cnt[i] > 0) atomicAdd(&counts[T.key[i]], T.cnt[i]);
 }
 
-__global__ void __launch_bounds__(SCAN_B) k_scan_sums(const int* __restrict__ counts, int nb,
-                                                      int* __restrict__ bsum) {
-  __shared__ int sh[SCAN_B];
-  const int i = blockIdx.x * SCAN_B + threadIdx.x;
-  const int v = i < nb ? counts[i] : 0;
-  const int incl = block_incl_scan(v, sh);
-  if (threadIdx.x == SCAN_B - 1) bsum[blockIdx.x] = incl;
+// Bank residues of a tile's cells.  In the push every LDS access of a
+// wavefront is the lanes' cell base addresses plus one offset common to
+// the lanes of one class (one stencil shape).  The LDS has 32 four-byte
+// banks and serves a wavefront's 4-byte accesses 32 lanes per cycle and its
+// 8-byte accesses (the current tile's atomics, the double-precision field
+// reads) 16 lanes per cycle, two banks each.  Lanes in one such group go
+// through without conflict when their cells' element indices in the region
+// differ modulo the group size; 32 consecutive distinct residues
+// modulo 32 are also 16 distinct residues modulo 16 in each half, so the
+// residue is taken modulo 32 in both precisions (replayed access patterns:
+// modulo 16 costs the double-precision gather and deposit 18 % more LDS
+// cycles).
+constexpr int RES = 32;
+static_assert(RES <= 32, "residue masks are 32-bit words");
+// Cells of a tile (at most; 8^3 in 3D, 16^2 in 2D).
+constexpr int TILE_CELLS_MAX = 512;
+__device__ __forceinline__ int cell_residue(const SortParams& S, int lc) {
+  const int lx = lc % S.T[0], ly = (lc / S.T[0]) % S.T[1], lz = lc / (S.T[0] * S.T[1]);
+  return (lx + S.rs1 * ly + S.rs2 * lz) % RES;
 }
 
-// one workgroup: exclusive scan of the nblk block sums in place
-__global__ void __launch_bounds__(SCAN_B) k_scan_blocks(int* __restrict__ bsum, int nblk) {
-  __shared__ int sh[SCAN_B];
+// Workgroup 0: exclusive scan of the tile counts (nb of them, the dead bin
+// last) into the scatter's cursors (in place) and the push's tile starts
+// (starts[t] = first particle of tile t, starts[nb - 1] = first absorbed
+// particle, starts[nb] = total), SCAN_PER counts per thread and pass.
+// Workgroup 1: a tile's cells by bank residue, order[0 .. ncells) = cells
+// sorted by (residue, cell), order[TILE_CELLS_MAX + r] = first entry of
+// residue r (r <= RES).  (Six launches of 2 to 9 us each before.)
+constexpr int SCAN_NT = 1024, SCAN_PER = 8;
+__global__ void __launch_bounds__(SCAN_NT) k_sort_scan(SortParams S, int* __restrict__ counts, int nb,
+                                                       int* __restrict__ starts,
+                                                       int* __restrict__ order) {
+  __shared__ int sh[SCAN_NT];
+  if (blockIdx.x == 1) {
+    __shared__ int cnt[RES];
+    const int ncells = S.T[0] * S.T[1] * S.T[2];
+    const int lc = threadIdx.x;
+    if (lc < RES) cnt[lc] = 0;
+    int r = 0;
+    if (lc < ncells) {
+      r = cell_residue(S, lc);
+      sh[lc] = r;
+    }
+    __syncthreads();
+    if (lc < ncells) atomicAdd(&cnt[r], 1);
+    __syncthreads();
+    if (lc < ncells) {
+      int pos = 0;
+      for (int q = 0; q < r; ++q) pos += cnt[q];
+      for (int c = 0; c < lc; ++c) pos += sh[c] == r;
+      order[pos] = lc;
+    }
+    if (lc <= RES) {
+      int st = 0;
+      for (int q = 0; q < lc; ++q) st += cnt[q];
+      order[TILE_CELLS_MAX + lc] = st;
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int carry = 0;
-  for (int base = 0; base < nblk; base += SCAN_B) {
-    const int i = base + threadIdx.x;
-    const int v = i < nblk ? bsum[i] : 0;
-    const int incl = block_incl_scan(v, sh);
-    if (i < nblk) bsum[i] = carry + incl - v;
-    carry += sh[SCAN_B - 1];
+  for (int base = 0; base < nb; base += SCAN_NT * SCAN_PER) {
+    const int i0 = base + (int)threadIdx.x * SCAN_PER;
+    int v[SCAN_PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_PER; ++k) {
+      v[k] = i0 + k < nb ? counts[i0 + k] : 0;
+      sum += v[k];
+    }
+    int incl = sum;  // over the wavefront's threads
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int x = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += x;
+    }
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    int before = carry, total = 0;  // earlier wavefronts, and all of them
+#pragma unroll
+    for (int q = 0; q < SCAN_NT / 64; ++q) {
+      if (q < wave) before += sh[q];
+      total += sh[q];
+    }
+    int ex = before + incl - sum;
+#pragma unroll
+    for (int k = 0; k < SCAN_PER; ++k) {
+      if (i0 + k < nb) {
+        starts[i0 + k] = ex;
+        counts[i0 + k] = ex;
+        if (i0 + k == nb - 1) starts[nb] = ex + v[k];
+      }
+      ex += v[k];
+    }
+    carry += total;
     __syncthreads();
   }
-}
-
-__global__ void __launch_bounds__(SCAN_B) k_scan_apply(int* __restrict__ counts, int nb,
-                                                       const int* __restrict__ bsum,
-                                                       int* __restrict__ starts) {
-  __shared__ int sh[SCAN_B];
-  const int i = blockIdx.x * SCAN_B + threadIdx.x;
-  const int v = i < nb ? counts[i] : 0;
-  const int incl = block_incl_scan(v, sh);
-  const int ex = bsum[blockIdx.x] + incl - v;
-  if (i < nb) {
-    starts[i] = ex;
-    counts[i] = ex;  // cursor for the scatter
-  }
-  if (i == nb - 1) starts[nb] = ex + v;
-}
-
-// Tile starts for the push: tstart[t] = first particle of tile t
-// (t = ntiles: first absorbed particle), tstart[ntiles + 1] = np.
-__global__ void k_tile_starts(const int* __restrict__ bstart, int ntiles, int* __restrict__ tstart) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t <= ntiles + 1) tstart[t] = bstart[t];
 }
 
 template <typename R>
@@ -208,9 +279,6 @@ struct SortArrays {
   R* t_q;
   int* t_id;
 };
-
-// Cells of a tile (at most; 8^3 in 3D, 16^2 in 2D).
-constexpr int TILE_CELLS_MAX = 512;
 
 // In-tile placement key of a live particle of tile t: its class (the half
 // of the cell along each axis) and its cell within the tile, both of the
@@ -259,59 +327,86 @@ __device__ __forceinline__ int placement_key(const SortParams& S, int t, int cl,
 }
 
 // Copies every particle to its tile's range of the scratch arrays (in the
-// order the atomics give) and records its in-tile placement key there.
+// order the atomics give) and records its in-tile placement key there.  A
+// workgroup takes SCATTER_PER particles per thread (chunks spread as above),
+// ranks them per tile in LDS and moves each tile's cursor once.
+// Bound by the scattered stores of ten arrays, in runs of a tile's share (FP32,
+// one MI355X: 16.8M warm particles 335 -> 270 us, 2.9M behind a moving window
+// 144 -> 41 us; with the count, 77 -> 41 and 116 -> 19 us).
+constexpr int SCATTER_NT = 256, SCATTER_PER = 4;
 template <typename R>
-__global__ void k_sort_scatter(SortArrays<R> A, SortParams S, long np, int ncell,
-                               const int* __restrict__ keys, int* __restrict__ cursor,
-                               int* __restrict__ pkey, DevFlags* flg) {
+__global__ void __launch_bounds__(SCATTER_NT) k_sort_scatter(SortArrays<R> A, SortParams S, long np,
+                                                             int ncell, int* __restrict__ cursor,
+                                                             int* __restrict__ pkey, DevFlags* flg) {
+  __shared__ TileTable T;
   const int dims = S.dims;
-  const long p = spread_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  const bool in = p < np;
-  // the payload is loaded first, so that its latency overlaps the cursor
-  // atomic's round trip
-  const int cl = in ? A.cell[p] : 0;
-  const int key = in ? keys[p] : -1;
-  R o[3] = {R(0), R(0), R(0)}, u[3] = {R(0), R(0), R(0)}, qv = R(0);
-  int idv = 0;
-  if (in) {
-    for (int d = 0; d < dims; ++d) o[d] = A.off[d][p];
-    for (int c = 0; c < 3; ++c) u[c] = A.u[c][p];
-    if (A.q) qv = A.q[p];
-    if (A.id) idv = A.id[p];
+  const long c0 = spread_block(blockIdx.x, gridDim.x) * (long)(SCATTER_NT * SCATTER_PER) + threadIdx.x;
+  // the payload is loaded first, so that its latency overlaps the ranking
+  struct {
+    int cl, id;
+    R o[3], u[3], q;
+  } v[SCATTER_PER];
+#pragma unroll
+  for (int k = 0; k < SCATTER_PER; ++k) {
+    const long p = c0 + k * SCATTER_NT;
+    const bool in = p < np;
+    v[k].cl = in ? A.cell[p] : 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) v[k].o[d] = in && d < dims ? A.off[d][p] : R(0);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[k].u[c] = in ? A.u[c][p] : R(0);
+    v[k].q = in && A.q ? A.q[p] : R(0);
+    v[k].id = in && A.id ? A.id[p] : 0;
   }
-  int head = 0, len = 64;
-  if (__ballot(key == __builtin_amdgcn_readfirstlane(key)) != ~0ull)  // else one run (usual)
-    wave_runs(key, head, len);
-  const int lane = threadIdx.x & 63;
-  int base = 0;
-  if (lane == head && key >= 0) base = atomicAdd(&cursor[key], len);
-  base = __shfl(base, head, 64);
+  table_clear(T);
+  __syncthreads();
+  int key[SCATTER_PER], slot[SCATTER_PER], rank[SCATTER_PER];
+#pragma unroll
+  for (int k = 0; k < SCATTER_PER; ++k) {
+    key[k] = c0 + k * SCATTER_NT < np ? tile_key(S, v[k].cl, ncell) : -1;
+    table_rank(T, key[k], slot[k], rank[k]);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < HT; i += SCATTER_NT)  // first position of each tile's share
+    if (T.cnt[i] > 0) T.cnt[i] = atomicAdd(&cursor[T.key[i]], T.cnt[i]);
   if (A.q) {
     // largest |q| as a float bit pattern (non-negative floats order as
     // unsigned integers), rounded up so that it bounds every |q| of type R
-    unsigned m = 0u;
-    if (in) {
-      const R qa = fabs(qv);
-      float f = (float)qa;
-      if ((R)f < qa) f = nextafterf(f, INFINITY);
-      m = __float_as_uint(f);
+    R qa = R(0);
+    bool nan = false;
+#pragma unroll
+    for (int k = 0; k < SCATTER_PER; ++k) {
+      qa = fmax(qa, (R)fabs(v[k].q));
+      nan = nan || v[k].q != v[k].q;
     }
+    float f = (float)qa;
+    if ((R)f < qa) f = nextafterf(f, INFINITY);
+    unsigned m = nan ? 0x7fc00000u : __float_as_uint(f);
     for (int sh = 32; sh > 0; sh >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, sh, 64));
     // every wavefront's atomic on the one word would serialize: skip it when
     // the maximum so far (a possibly stale read, which can only cost an
     // extra atomic) already covers this wavefront's
-    if (lane == 0 && m > __hip_atomic_load(&flg->qmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    if ((threadIdx.x & 63) == 0 &&
+        m > __hip_atomic_load(&flg->qmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       atomicMax(&flg->qmax, m);
   }
-  if (!in) return;
-  const long dst = (long)base + (lane - head);
-  const bool live = cl >= 0 && cl < ncell;
-  if (live) pkey[dst] = placement_key<R>(S, key, cl, o, u);
-  A.t_cell[dst] = live ? cl : -1;
-  for (int d = 0; d < dims; ++d) A.t_off[d][dst] = o[d];
-  for (int c = 0; c < 3; ++c) A.t_u[c][dst] = u[c];
-  if (A.id) A.t_id[dst] = idv;
-  if (A.q) A.t_q[dst] = qv;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < SCATTER_PER; ++k) {
+    if (key[k] < 0) continue;
+    // (slot < 0: the table had no slot)
+    const long dst = slot[k] >= 0 ? (long)T.cnt[slot[k]] + rank[k] : (long)atomicAdd(&cursor[key[k]], 1);
+    const bool live = v[k].cl >= 0 && v[k].cl < ncell;
+    if (live) pkey[dst] = placement_key<R>(S, key[k], v[k].cl, v[k].o, v[k].u);
+    A.t_cell[dst] = live ? v[k].cl : -1;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (d < dims) A.t_off[d][dst] = v[k].o[d];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) A.t_u[c][dst] = v[k].u[c];
+    if (A.id) A.t_id[dst] = v[k].id;
+    if (A.q) A.t_q[dst] = v[k].q;
+  }
 }
 
 // One particle's payload in registers: every load first, then every store
@@ -342,55 +437,6 @@ struct PVal {
     if (A.id) const_cast<int*>(A.id)[j] = id;
   }
 };
-
-// Bank residues of a tile's cells.  In the push every LDS access of a
-// wavefront is the lanes' cell base addresses plus one offset common to
-// the lanes of one class (one stencil shape).  The LDS has 32 four-byte
-// banks and serves a wavefront's 4-byte accesses 32 lanes per cycle and its
-// 8-byte accesses (the current tile's atomics, the double-precision field
-// reads) 16 lanes per cycle, two banks each.  Lanes in one such group go
-// through without conflict when their cells' element indices in the region
-// differ modulo the group size; 32 consecutive distinct residues
-// modulo 32 are also 16 distinct residues modulo 16 in each half, so the
-// residue is taken modulo 32 in both precisions (replayed access patterns:
-// modulo 16 costs the double-precision gather and deposit 18 % more LDS
-// cycles).  One workgroup lists the tile's cells by residue:
-// order[0 .. ncells) = cells sorted by (residue, cell),
-// order[TILE_CELLS_MAX + r] = first entry of residue r (r <= RES).
-constexpr int ORDER_NT = 512;
-constexpr int RES = 32;
-static_assert(RES <= 32, "residue masks are 32-bit words");
-__device__ __forceinline__ int cell_residue(const SortParams& S, int lc) {
-  const int lx = lc % S.T[0], ly = (lc / S.T[0]) % S.T[1], lz = lc / (S.T[0] * S.T[1]);
-  return (lx + S.rs1 * ly + S.rs2 * lz) % RES;
-}
-
-__global__ void __launch_bounds__(ORDER_NT) k_sort_order(SortParams S, int* __restrict__ order) {
-  __shared__ int cnt[RES];
-  __shared__ int res[ORDER_NT];
-  const int ncells = S.T[0] * S.T[1] * S.T[2];
-  const int lc = threadIdx.x;
-  if (lc < RES) cnt[lc] = 0;
-  int r = 0;
-  if (lc < ncells) {
-    r = cell_residue(S, lc);
-    res[lc] = r;
-  }
-  __syncthreads();
-  if (lc < ncells) atomicAdd(&cnt[r], 1);
-  __syncthreads();
-  if (lc < ncells) {
-    int pos = 0;
-    for (int q = 0; q < r; ++q) pos += cnt[q];
-    for (int c = 0; c < lc; ++c) pos += res[c] == r;
-    order[pos] = lc;
-  }
-  if (lc <= RES) {
-    int st = 0;
-    for (int q = 0; q < lc; ++q) st += cnt[q];
-    order[TILE_CELLS_MAX + lc] = st;
-  }
-}
 
 // Placement of one tile's particles (one workgroup per tile) from the
 // scatter's copy back into the particle arrays.  Pass 1 gives every particle
@@ -681,26 +727,19 @@ static int launch_sort_t(const pic_ctx* ctx, const pic_particles* p, void* ws, h
   char* w = (char*)ws;
   int* counts = (int*)(w + L.counts);
   int* starts = (int*)(w + L.starts);
-  int* bstart = (int*)(w + L.bstart);
-  int* bsum = (int*)(w + L.bsum);
-  int* keys = (int*)(w + L.keys);
   const int nb = S.ntiles + 1;  // + dead bin
-  const int nblk = (nb + SCAN_B - 1) / SCAN_B;
   if (np == 0) {
     k_fill_int<<<dim3((S.ntiles + 2 + 255) / 256), dim3(256), 0, s>>>(starts, S.ntiles + 2, 0);
     return (int)hipGetLastError();
   }
   auto fill_grid = [](long n) { return dim3((unsigned)((n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384)); };
   k_fill_int<<<fill_grid(nb), dim3(256), 0, s>>>(counts, nb, 0);
-  const unsigned grid = (unsigned)((np + 255) / 256);
   DevFlags* flg = (DevFlags*)(w + L.flags);
-  const long cchunk = (long)COUNT_NT * COUNT_PER;
+  int* order = (int*)(w + L.order);
+  const long cchunk = (long)COUNT_NT * COUNT_PER, schunk = (long)SCATTER_NT * SCATTER_PER;
   k_sort_count<<<dim3((unsigned)((np + cchunk - 1) / cchunk)), dim3(COUNT_NT), 0, s>>>(
-      S, p->cell, np, ncell, keys, counts, flg);
-  k_scan_sums<<<dim3(nblk), dim3(SCAN_B), 0, s>>>(counts, nb, bsum);
-  k_scan_blocks<<<dim3(1), dim3(SCAN_B), 0, s>>>(bsum, nblk);
-  k_scan_apply<<<dim3(nblk), dim3(SCAN_B), 0, s>>>(counts, nb, bsum, bstart);
-  k_tile_starts<<<dim3((S.ntiles + 2 + 255) / 256), dim3(256), 0, s>>>(bstart, S.ntiles, starts);
+      S, p->cell, np, ncell, counts, flg);
+  k_sort_scan<<<dim3(2), dim3(SCAN_NT), 0, s>>>(S, counts, nb, starts, order);
   SortArrays<R> A;
   A.cell = p->cell;
   R* tr = (R*)(w + L.tmp_real);
@@ -716,9 +755,8 @@ static int launch_sort_t(const pic_ctx* ctx, const pic_particles* p, void* ws, h
   A.t_cell = (int*)(w + L.tmp_cell);
   A.t_id = (int*)(w + L.tmp_id);
   int* pkey = (int*)(w + L.pkey);
-  k_sort_scatter<R><<<dim3(grid), dim3(256), 0, s>>>(A, S, np, ncell, keys, counts, pkey, flg);
-  int* order = (int*)(w + L.order);
-  k_sort_order<<<dim3(1), dim3(ORDER_NT), 0, s>>>(S, order);
+  k_sort_scatter<R><<<dim3((unsigned)((np + schunk - 1) / schunk)), dim3(SCATTER_NT), 0, s>>>(
+      A, S, np, ncell, counts, pkey, flg);
   k_sort_place<R><<<dim3((unsigned)S.ntiles), dim3(PLACE_NT), 0, s>>>(A, S, starts, order, pkey, c.dims);
   // absorbed particles (the dead bin) are not copied back: the caller lowers
   // np to the live count, starts[ntiles]

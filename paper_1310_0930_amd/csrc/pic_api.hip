@@ -28,8 +28,6 @@ WsLayout ws_layout(const pic_ctx* ctx, int64_t np) {
   off = align256(off + sizeof(int) * nbins);
   L.bstart = off;
   off = align256(off + sizeof(int) * (nbins + 1));
-  L.bsum = off;
-  off = align256(off + sizeof(int) * (nbins / 1024 + 1));
   L.rb_tv = off;
   off = align256(off + sizeof(int) * (size_t)ctx->ntiles);
   L.rb_nl = off;

@@ -211,10 +211,9 @@ struct WsLayout {
   size_t starts;     // int32[ntiles + 2]   tile starts (entry ntiles = dead bin start, then np)
   size_t counts;     // int32[nbins]        bin counts / scatter cursors
   size_t bstart;     // int32[nbins + 1]    bin starts
-  size_t bsum;       // int32[nbins / 1024 + 1]  scan block sums
   size_t rb_tv;      // int32[ntiles]       re-binned pass: slot of each destination tile
   size_t rb_nl;      // int32[ntiles]       re-binned pass: destination tiles
-  size_t keys;       // int32[np]           tile of each particle (count, scatter)
+  size_t keys;       // int32[np]           re-binned pass: ranks of the deferred particles
   size_t pkey;       // int32[np]           in-tile placement key of each copied particle, then its rank
   size_t order;      // int32[1024]         a tile's cells listed by bank residue
   size_t tmp_cell;   // int32[np]
