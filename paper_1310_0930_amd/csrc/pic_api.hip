@@ -11,7 +11,7 @@
 #include "pic_internal.h"
 
 namespace pic {
-long diag_len(const pic_config& cf);
+long diag_len(const pic_config& cf, int ntiles);
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -32,7 +32,7 @@ WsLayout ws_layout(const pic_ctx* ctx, int64_t np) {
   off = align256(off + sizeof(int) * (size_t)ctx->ntiles);
   L.rb_nl = off;
   off = align256(off + sizeof(int) * (size_t)ctx->ntiles);
-  L.diag_len = (size_t)diag_len(ctx->cfg);
+  L.diag_len = (size_t)diag_len(ctx->cfg, ctx->ntiles);
   L.diag = off;
   off = align256(off + sizeof(double) * L.diag_len);
   const size_t n = np > 0 ? (size_t)np : 0;
@@ -514,18 +514,8 @@ int pic_diagnostics_species(int32_t nspecies, pic_ctx* const* ctx, const pic_par
   if ((v = check_fields(f, true))) return v;
   if ((v = ensure_device(ctx[0]))) return v;
   memset(out, 0, sizeof(*out));
-  v = hip_status(launch_diagnostics(nspecies, ctx, p, ws, f, rho_prev, gauss_ref, rho_out,
-                                    gauss_out, out, (hipStream_t)stream));
-  if (v) return v;
-  for (int32_t k = 0; k < nspecies; ++k) {
-    uint32_t flags = 0;
-    int64_t slow = 0;
-    v = pic_read_flags(ctx[k], ws[k], 0, &flags, &slow, stream);
-    if (v != PIC_OK && v != PIC_EDEVICE) return v;
-    out->flags |= flags;
-    out->n_slowpath += slow;
-  }
-  return PIC_OK;
+  return hip_status(launch_diagnostics(nspecies, ctx, p, ws, f, rho_prev, gauss_ref, rho_out,
+                                       gauss_out, out, (hipStream_t)stream));
 }
 
 int pic_diagnostics(pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
