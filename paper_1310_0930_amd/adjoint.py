@@ -96,12 +96,15 @@ class Runner:
         starts = sorted(self.checkpoints)
         for k, n0 in reversed(list(enumerate(starts))):
             n1 = starts[k + 1] if k + 1 < len(starts) else self.steps
-            # recompute the segment, keeping each step's input state
-            self._restore(self.checkpoints[n0])
-            states = []
-            for n in range(n0, n1):
-                states.append(self._state())
-                self._step()
+            # recompute the segment, keeping each step's input state: the first
+            # is the checkpoint itself and the last stays in the simulation,
+            # whose own step nothing needs
+            states = [self.checkpoints[n0]]
+            if n1 - n0 > 1:
+                self._restore(states[0])
+                for n in range(n0 + 1, n1):
+                    self._step()
+                    states.append(self._state() if n + 1 < n1 else (s.cell, s.off, s.u, s.E, s.B))
             for n in reversed(range(n0, n1)):
                 cell, off, u, E, B = states[n - n0]
                 parts = P.particles_struct(s.np, cell, off, u, s.q)
