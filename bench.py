@@ -489,7 +489,7 @@ def cpu_baseline(w, log, budget_s=12.0):
 # which bench runs read for ``roofline.traffic`` while the push kernel's
 # sources are unchanged.
 
-_STEP_START = ("k_push", "k_sort", "k_pda", "k_adj_reset", "k_fill_int", "k_scan", "k_tile_starts")
+_STEP_START = ("k_push", "k_sort", "k_pda", "k_adj_reset", "k_fill_int")
 
 
 def _rp_rows(d, suffix):
@@ -516,8 +516,8 @@ def _rp_field_grids():
     for w in I.WORKLOADS.values():
         n = w.n3 if w.dims == 3 else (w.n3[0], w.n3[1], 1)
         ncell = n[0] * n[1] * n[2]
-        col = w.dims == 3 and all(b == 0 for b in w.bc3) and n[2] % 4 == 0
-        blocks = -(-(ncell // 4 if col else ncell) // 256)
+        col = w.dims == 3 and ncell >= 1 << 19  # a thread takes four planes
+        blocks = -(-(n[0] * n[1] * -(-n[2] // 4) if col else ncell) // 256)
         out.setdefault(str((blocks + 7) // 8 * 8 * 256), w.name)
     return out
 

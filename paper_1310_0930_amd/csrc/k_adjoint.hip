@@ -881,10 +881,10 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
   }
 }
 
-__global__ void k_adj_reset(DevFlags* flg) { flg->ndefer = 0u; }
+static __global__ void k_adj_reset(DevFlags* flg) { flg->ndefer = 0u; }
 
 template <int DIMS, int ORDER, typename R>
-static int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
+int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
                       const pic_fields* lf, pic_particles* lp, void* ws, hipStream_t s) {
   KParams<R> P = make_params<R>(ctx);
   WsLayout Lw = ws_layout(ctx, p->np);
@@ -946,6 +946,20 @@ static int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fiel
   return (int)hipGetLastError();
 }
 
+// The instantiations are compiled one by one (the build defines PIC_DIMS,
+// PIC_ORDER and PIC_REAL), the dispatch in a part of its own: one compiler takes
+// many times as long for all of them.
+#define PIC_INST(HOW, DD, OO, RR) \
+  HOW template int launch_pda<DD, OO, RR>( \
+      const pic_ctx* ctx, const pic_particles* p, const pic_fields* f, \
+      const pic_fields* lf, pic_particles* lp, void* ws, hipStream_t s);
+#ifdef PIC_DIMS
+PIC_INST(, PIC_DIMS, PIC_ORDER, PIC_REAL)
+#else
+#define PIC_EXTERN(DD, OO) PIC_INST(extern, DD, OO, float) PIC_INST(extern, DD, OO, double)
+PIC_EXTERN(2, 1) PIC_EXTERN(2, 2) PIC_EXTERN(2, 3) PIC_EXTERN(2, 4)
+PIC_EXTERN(3, 1) PIC_EXTERN(3, 2) PIC_EXTERN(3, 3) PIC_EXTERN(3, 4)
+
 int launch_push_deposit_adjoint(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
                                 const pic_fields* lam_f, pic_particles* lam_p, void* ws,
                                 hipStream_t s) {
@@ -960,5 +974,6 @@ int launch_push_deposit_adjoint(const pic_ctx* ctx, const pic_particles* p, cons
 #undef PIC_PDA
   return (int)hipErrorInvalidValue;
 }
+#endif
 
 }  // namespace pic

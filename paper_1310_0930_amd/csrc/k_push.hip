@@ -749,7 +749,7 @@ __global__ void __launch_bounds__(256) k_push_deferred(KParams<R> P, DParts<R> p
 // the tile counters behind the first tiles of the two tile passes' workgroups
 // (grid and rb_grid of them).
 template <typename R>
-__global__ void k_push_prologue(R* a, R* b, R* c, long n, DevFlags* flg, int* rb_cnt, int ntiles,
+static __global__ void k_push_prologue(R* a, R* b, R* c, long n, DevFlags* flg, int* rb_cnt, int ntiles,
                                 unsigned grid, unsigned rb_grid) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     flg->since_sort += flg->ndefer;
@@ -803,7 +803,7 @@ static unsigned tile_grid(const KParams<R>& P) {
 }
 
 template <int DIMS, int ORDER, typename R>
-static int launch_pd(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f, void* ws,
+int launch_pd(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f, void* ws,
                      hipStream_t s, bool accumulate) {
   using G = Geo<DIMS, ORDER, R>;
   KParams<R> P = make_params<R>(ctx);
@@ -857,6 +857,20 @@ static int launch_pd(const pic_ctx* ctx, const pic_particles* p, const pic_field
   return (int)hipGetLastError();
 }
 
+// The instantiations are compiled one by one (the build defines PIC_DIMS,
+// PIC_ORDER and PIC_REAL), the dispatch in a part of its own: one compiler takes
+// many times as long for all of them.
+#define PIC_INST(HOW, DD, OO, RR) \
+  HOW template int launch_pd<DD, OO, RR>( \
+      const pic_ctx* ctx, const pic_particles* p, const pic_fields* f, \
+      void* ws, hipStream_t s, bool accumulate);
+#ifdef PIC_DIMS
+PIC_INST(, PIC_DIMS, PIC_ORDER, PIC_REAL)
+#else
+#define PIC_EXTERN(DD, OO) PIC_INST(extern, DD, OO, float) PIC_INST(extern, DD, OO, double)
+PIC_EXTERN(2, 1) PIC_EXTERN(2, 2) PIC_EXTERN(2, 3) PIC_EXTERN(2, 4)
+PIC_EXTERN(3, 1) PIC_EXTERN(3, 2) PIC_EXTERN(3, 3) PIC_EXTERN(3, 4)
+
 int launch_push_deposit(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f, void* ws,
                         hipStream_t s, bool accumulate) {
   const int D = ctx->cfg.dims, O = ctx->cfg.order;
@@ -870,5 +884,6 @@ int launch_push_deposit(const pic_ctx* ctx, const pic_particles* p, const pic_fi
 #undef PIC_PD
   return (int)hipErrorInvalidValue;
 }
+#endif
 
 }  // namespace pic
