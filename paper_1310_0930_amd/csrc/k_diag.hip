@@ -6,8 +6,6 @@
 // (Sec. 5.2: a charge-conserving method for the virtual trajectories); these
 // residuals measure it in double precision against the positions the push
 // actually stored, whatever precision the push ran in.
-#include <type_traits>
-
 #include "k_common.h"
 
 namespace pic {
@@ -142,9 +140,12 @@ __device__ __forceinline__ void store_kinetic(double wk, double alive, double* p
 // agree, modulo the 16 eight-byte banks, with those by which the sort spread
 // the lanes of a wavefront (dense rows and planes make them collide).  With
 // part the kernel also takes the particles' kinetic energy, whose loads hide
-// behind the atomics (FP32, quadratic, 10M particles on one MI355X: 123 us, the
-// LDS busy 53 % of them and the VALU 51 %, and 179 us with double adds; before
-// 200 us and 48 us for a pass of their own).
+// behind the atomics (FP32, quadratic, 10M particles on one MI355X: 179 us, the
+// LDS busy 71 % of them; before 200 us and 48 us for a pass of their own).  The
+// sums stay in double: as 64-bit integers on one scale they took 123 us, but a
+// weight then keeps no digits of its own, and nodes at the edge of a plasma,
+// which hold only small weights, were off by 1e-12 (2D quadratic) to 2e-6
+// (quartic) of their charge.
 struct RhoTiles {
   int ntile[3];
   const int* starts;  // tile t holds particles starts[t] .. starts[t+1]-1
@@ -152,15 +153,7 @@ struct RhoTiles {
 
 constexpr int like_mod16(int least, int want) { return least + ((want - least) % 16 + 16) % 16; }
 
-// FIXED: the region sums the weights as 64-bit integers, whose LDS adds take
-// half the cycles of double adds, and the charge multiplies each node's sum
-// once.  A weight is rounded once, to half of 2^-WBITS, and the sums are exact;
-// a double sum is rounded at every weight.  Which of the two is closer
-// (rho_fixed) is a matter of how many weights a node takes: against extended
-// precision, in units of 1e-16 of the largest density, quadratic 3D 0.65
-// (double 2.1) at 8 per cell, 0.75 (0.94) at 2, 0.77 (0.60) at 1; quartic 1.05
-// (1.8) at 2; quadratic 2D 0.55 (2.1) at 16, 0.69 (0.97) at 4, 0.92 (0.51) at 1.
-template <int DIMS, int ORDER, typename R, bool FIXED>
+template <int DIMS, int ORDER, typename R>
 __global__ void __launch_bounds__(256) k_rho_tile(DiagParams P, RhoTiles Tl,
                                                   const int* __restrict__ cell, const R* o0,
                                                   const R* o1, const R* o2, const R* q, double qc,
@@ -174,8 +167,7 @@ __global__ void __launch_bounds__(256) k_rho_tile(DiagParams P, RhoTiles Tl,
   static_assert(HI - LO <= ORDER + 1, "the region holds every node a particle reaches");
   constexpr int RS = like_mod16(RX, G::sgl ? G::es : G::jb);
   constexpr int RP = DIMS == 3 ? like_mod16(RS * (RX - 1) + RX, G::sgl ? G::ep : G::jc) : RS * RX;
-  using Sum = typename std::conditional<FIXED, unsigned long long, double>::type;
-  __shared__ Sum reg[RP * RZ];
+  __shared__ double reg[RP * RZ];
   const int t = blockIdx.x;
   const int beg = Tl.starts[t], end = Tl.starts[t + 1];
   if (beg == end) {
@@ -185,12 +177,7 @@ __global__ void __launch_bounds__(256) k_rho_tile(DiagParams P, RhoTiles Tl,
   const int org[3] = {(t % Tl.ntile[0]) * G::T, ((t / Tl.ntile[0]) % Tl.ntile[1]) * G::T,
                       DIMS == 3 ? (t / (Tl.ntile[0] * Tl.ntile[1])) * G::TZ : 0};
   const int rlo[3] = {org[0] - G::A + LO, org[1] - G::A + LO, DIMS == 3 ? org[2] - G::AZ + LO : 0};
-  for (int r = threadIdx.x; r < RP * RZ; r += blockDim.x) reg[r] = Sum(0);
-  // the largest product of weights, (3/4, 2/3, 115/192)^D, stays below 2^52 on
-  // this scale, and the sum of 4096 below 2^64
-  constexpr int WBITS = DIMS == 3 ? (ORDER == 4 ? 54 : 53) : (ORDER == 2 ? 52 : 53);
-  const int more = end - beg > 4096 ? 32 - __clz(end - beg - 1) - 12 : 0;
-  const double scale = __longlong_as_double((long long)(1023 + WBITS - more) << 52);
+  for (int r = threadIdx.x; r < RP * RZ; r += blockDim.x) reg[r] = 0.0;
   __syncthreads();
   const R* off[3] = {o0, o1, o2};
   constexpr int M = ORDER + 1;
@@ -234,25 +221,15 @@ __global__ void __launch_bounds__(256) k_rho_tile(DiagParams P, RhoTiles Tl,
       inside = inside && v >= -Ad && v < Td + Ad;
     }
     if (inside) {
-      Sum* at = reg + (l[0] + G::A - LO + b[0]) + (l[1] + G::A - LO + b[1]) * RS +
+      double* at = reg + (l[0] + G::A - LO + b[0]) + (l[1] + G::A - LO + b[1]) * RS +
                    (DIMS == 3 ? (l[2] + G::AZ - LO + b[2]) * RP : 0);
 #pragma unroll
       for (int k = 0; k < MZ; ++k)
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-          const double wjk = (FIXED ? scale : qp) * w[1][j] * w[2][k];
+          const double wjk = qp * w[1][j] * w[2][k];
 #pragma unroll
-          for (int i = 0; i < M; ++i) {
-            if constexpr (FIXED) {
-              // (weights are not negative) adding 2^52 rounds to an integer,
-              // the low mantissa bits
-              const double y = fma(wjk, w[0][i], 4503599627370496.0);
-              atomicAdd(at + i + j * RS + k * RP,
-                        (unsigned long long)__double_as_longlong(y) - 0x4330000000000000ull);
-            } else {
-              atomicAdd(at + i + j * RS + k * RP, wjk * w[0][i]);
-            }
-          }
+          for (int i = 0; i < M; ++i) atomicAdd(at + i + j * RS + k * RP, wjk * w[0][i]);
         }
       continue;
     }
@@ -269,11 +246,7 @@ __global__ void __launch_bounds__(256) k_rho_tile(DiagParams P, RhoTiles Tl,
   __syncthreads();
   for (int r = threadIdx.x; r < RX * RX * RZ; r += blockDim.x) {
     const int rx = r % RX, ry = (r / RX) % RX, rz = r / (RX * RX);
-    double v;
-    if constexpr (FIXED)
-      v = qc * ((double)reg[rx + ry * RS + rz * RP] / scale);
-    else
-      v = reg[rx + ry * RS + rz * RP];
+    const double v = reg[rx + ry * RS + rz * RP];
     if (v == 0.0) continue;
     const int ix = axis_slot(rlo[0] + rx, P.n[0], P.open[0], 0);
     const int iy = axis_slot(rlo[1] + ry, P.n[1], P.open[1], 0);
@@ -469,20 +442,10 @@ static void rho_t(const DiagParams& P, const pic_particles* p, double qc, double
   const long np = p->np;
   if (np == 0) return;
   if (tiles) {
-    auto go = [&](auto fixed) {
-      k_rho_tile<DIMS, ORDER, R, decltype(fixed)::value><<<dim3((unsigned)ntiles), dim3(256), 0, s>>>(
-          P, *tiles, p->cell, (const R*)p->off[0], (const R*)p->off[1], (const R*)p->off[2],
-          (const R*)p->q, qc, (const R*)p->u[0], (const R*)p->u[1], (const R*)p->u[2], kin.minv, rho,
-          kin.part);
-    };
-    // Charges of their own per particle may have a wide range, linear shapes
-    // have few weights and leave those of up to 1 fewer bits, and below about
-    // 2 particles per cell double sums are the closer ones.
-    const bool rho_fixed = ORDER > 1 && !p->q && 2 * np >= 3 * (long)P.ncell;
-    if (rho_fixed)
-      go(std::integral_constant<bool, (ORDER > 1)>{});
-    else
-      go(std::false_type{});
+    k_rho_tile<DIMS, ORDER, R><<<dim3((unsigned)ntiles), dim3(256), 0, s>>>(
+        P, *tiles, p->cell, (const R*)p->off[0], (const R*)p->off[1], (const R*)p->off[2],
+        (const R*)p->q, qc, (const R*)p->u[0], (const R*)p->u[1], (const R*)p->u[2], kin.minv, rho,
+        kin.part);
     return;
   }
   k_deposit_rho<DIMS, ORDER, R><<<dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s>>>(
