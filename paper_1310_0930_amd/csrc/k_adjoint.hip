@@ -60,11 +60,11 @@ __device__ __forceinline__ int sample_index(const KParams<R>& P, int dims, bool 
 
 // Sample access of the adjoint helpers.  ref(comp, first) fixes the first
 // stencil node of a field component (0..2 E, 3..5 B), at(r, i, j, k) reads the
-// field and add(r, i, j, k, a, factor(b)) adds a b to its adjoint at compile-time
-// offsets from it; jref and jat do the same for lamJ.  AdjGlobal goes to the global arrays
+// field and add(r, i, j, k, v) adds to its adjoint at compile-time offsets from
+// it; jref and jat do the same for lamJ.  AdjGlobal goes to the global arrays
 // with the domain's wrap and open faces; AdjLds to a tile's LDS regions
 // (coordinates relative to the tile origin), the lamE/lamB region accumulating
-// in double, or for PDA_GATHER in FP32 in 64-bit fixed point (fixed_scale).
+// in double.
 template <int DIMS, typename R>
 struct AdjGlobal {
   const KParams<R>& P;
@@ -83,10 +83,9 @@ struct AdjGlobal {
     const int g = index(r, i, j, k);
     return g < 0 ? R(0) : (r.comp >= 3 ? F.B[r.comp - 3] : F.E[r.comp])[g];
   }
-  __device__ __forceinline__ R factor(R b) const { return b; }
-  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R a, R b) const {
+  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R v) const {
     const int g = index(r, i, j, k);
-    if (g >= 0) atomicAdd(&(r.comp >= 3 ? lamB[r.comp - 3] : lamE[r.comp])[g], a * b);
+    if (g >= 0) atomicAdd(&(r.comp >= 3 ? lamB[r.comp - 3] : lamE[r.comp])[g], v);
   }
   __device__ __forceinline__ Ref jref(int comp, const int* b) const { return ref(comp, b); }
   __device__ __forceinline__ R jat(const Ref& r, int i, int j, int k) const {
@@ -101,10 +100,12 @@ struct AdjGlobal {
 // registers, so that a CU held 8 wavefronts and neither its LDS nor its
 // arithmetic was half used (96x80x64 quadratic FP32: 1237 us); there PDA_BACK
 // goes from the step's outputs back to the adjoints of the interpolated fields
-// (E/B and lamJ in LDS; 265 us, the VALU 70 % busy) and leaves those six values
+// (E/B and lamJ in LDS; 262 us, the VALU 73 % busy) and leaves those six values
 // in scratch, and PDA_GATHER transposes the gather (E/B and lamE/lamB in LDS;
-// 395 us, the LDS 57 % busy with 162 adds per particle; in double adds, which
-// take it twice as long, 535 us).
+// 535 us, the LDS 69 % busy: 162 double adds of at least 8 LDS cycles per
+// 64 particles; as 64-bit integers on one scale per tile the adds took 395 us,
+// but a tile's small adjoints lost their digits beside its large ones, at 1e-14
+// of them half of their value).
 enum { PDA_ALL = 0, PDA_BACK = 1, PDA_GATHER = 2 };
 
 // Region of one workgroup of the LDS adjoint: the push tile, cut along z
@@ -117,7 +118,6 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   using B = Geo<DIMS, ORDER, R>;
   using Rc = typename B::Rc;
   static constexpr bool has_lj = PHASE != PDA_GATHER, has_leb = PHASE != PDA_BACK;
-  static constexpr bool fixed_leb = PHASE == PDA_GATHER && sizeof(R) == 4;
   static constexpr size_t bytes(int tz) {
     return (sizeof(R) * 6 + (has_leb ? sizeof(double) * 6 : 0)) *
                (size_t)(B::ex * B::ex * (tz + 2 * B::AZ + Rc::g_hi - Rc::g_lo)) +
@@ -150,24 +150,11 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   static constexpr int j_vol = B::jx * B::jx * jz;
 };
 
-// Scale of the fixed-point sums of a tile of n particles whose interpolated
-// adjoints are at most `big` in magnitude (finite): a power of two that takes
-// them to at most 2^50, less where more than 4096 particles could add up to
-// 2^62.  A contribution is rounded once, to 2^-51 of `big` (in double it was
-// rounded to 24 bits as a product and the sum of m of them m times to 53); 64-bit
-// integer adds take 4 LDS cycles where double adds take 8.
-__device__ __forceinline__ double fixed_scale(float big, int n) {
-  const int e = (int)((__float_as_uint(big) >> 23) & 255u) - 126;  // big < 2^e
-  const int more = n > 4096 ? 32 - __clz(n - 1) - 12 : 0;
-  return __longlong_as_double((long long)(1023 + 50 - more - e) << 52);
-}
-
 template <int DIMS, int ORDER, typename R, class G>
 struct AdjLds {
   lds_ptr<const R> eb;   // E^n (0..2), B^n (3..5) over the field region
   lds_ptr<const R> lj;   // lamJ over the current region
   lds_ptr<double> leb;   // lamE (0..2), lamB (3..5) over the field region
-  double scale;          // of the fixed-point sums (G::fixed_leb)
   struct Ref {
     lds_ptr<const R> f;
     lds_ptr<double> l;
@@ -189,34 +176,9 @@ struct AdjLds {
     using vptr = __attribute__((address_space(3))) const volatile R*;
     return ((vptr)r.f)[k * G::ep + j * G::es + i];
   }
-  using C = typename std::conditional<G::fixed_leb, double, R>::type;
-  __device__ __forceinline__ C factor(R b) const {
-    if constexpr (G::fixed_leb)
-      return (double)b * scale;
-    else
-      return b;
-  }
-  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R a, C b) const {
-    const lds_ptr<double> t = &r.l[k * G::ep + j * G::es + i];
-    if constexpr (G::fixed_leb) {
-      // |a b| < 2^51: adding 1.5 * 2^52 rounds it to an integer in the low
-      // mantissa bits (one rounding, fused), whose two's complement is the
-      // bit pattern less that of the constant
-      const double y = fma((double)a, b, 6755399441055744.0);
-      const unsigned long long n =
-          (unsigned long long)__double_as_longlong(y) - 0x4338000000000000ull;
-      __hip_atomic_fetch_add((lds_ptr<unsigned long long>)t, n, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-      __hip_atomic_fetch_add(t, (double)(a * b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-  }
-  // A node's sum.
-  static __device__ __forceinline__ double sum(double v, double inv_scale) {
-    if constexpr (G::fixed_leb)
-      return (double)__double_as_longlong(v) * inv_scale;
-    else
-      return v;
+  __device__ __forceinline__ void add(const Ref& r, int i, int j, int k, R v) const {
+    __hip_atomic_fetch_add(&r.l[k * G::ep + j * G::es + i], (double)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   __device__ __forceinline__ lds_ptr<const R> jref(int comp, const int* b) const {
     return pin<const R>(lj + (DIMS == 3 ? (b[2] - G::j_lo_z) * G::jx * G::jx : 0) +
@@ -248,13 +210,13 @@ __device__ __forceinline__ void gather_vjp_comp(const Acc& ac, int comp, const i
 #pragma unroll
     for (int j = 0; j < M; ++j) {
       R sx = R(0), dxx = R(0);
-      const auto lyz = ac.factor(w[1][j] * lz);
+      const R lyz = w[1][j] * lz;
 #pragma unroll
       for (int i = 0; i < M; ++i) {
         const R f = ac.at(r, i, j, k);
         sx += w[0][i] * f;
         dxx += dw[0][i] * f;
-        ac.add(r, i, j, k, w[0][i], lyz);
+        ac.add(r, i, j, k, w[0][i] * lyz);
       }
       s += w[1][j] * sx;
       dy += dw[1][j] * sx;
@@ -657,15 +619,12 @@ __global__ void __launch_bounds__(256) k_push_deposit_adjoint(KParams<R> P, DPar
 // outside the tile's drift allowance, or moving half a cell or more, go to the
 // list for the global-memory kernel (entered by PDA_ALL or PDA_BACK, which has
 // one slab); PDA_BACK leaves zeros in `lam_eb` (6 arrays of np) for the ones
-// that moved too far or became non-finite, and PDA_GATHER skips zeros.  In FP32
-// PDA_BACK also leaves each tile's largest such value for PDA_GATHER's scale
-// (tile_big); particles with an infinite or NaN one go to the list.
+// that moved too far or became non-finite, and PDA_GATHER skips zeros.
 template <int DIMS, int ORDER, typename R, int PHASE>
 __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
                                   (AdjGeo<DIMS, ORDER, R, PHASE>::WPE)) k_pda_tile(
     KParams<R> P, DParts<R> pa, DFields<R> F, DFields<R> L, DParts<R> lam, R* __restrict__ lam_eb,
-    unsigned* __restrict__ tile_big, long np, const int* __restrict__ starts,
-    int* __restrict__ deferred, DevFlags* flg) {
+    long np, const int* __restrict__ starts, int* __restrict__ deferred, DevFlags* flg) {
   using G = AdjGeo<DIMS, ORDER, R, PHASE>;
   constexpr int S = G::S;
   __shared__ R s_eb[6 * G::e_vol];
@@ -711,16 +670,11 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
       }
     }
   }
-  __shared__ unsigned s_big;  // PDA_BACK: the tile's largest |v|, bits of a float
-  if (PHASE == PDA_BACK && threadIdx.x == 0) s_big = 0u;
-  unsigned big = 0u;
   if constexpr (G::has_leb)
     for (int i = threadIdx.x; i < 6 * G::e_vol; i += G::NT) s_leb[i] = 0.0;
   __syncthreads();
-  const double scale =
-      G::fixed_leb ? fixed_scale(__uint_as_float(tile_big[tile]), pend - pbeg) : 1.0;
   const AdjLds<DIMS, ORDER, R, G> ac{(lds_ptr<const R>)s_eb, (lds_ptr<const R>)s_lj,
-                                     (lds_ptr<double>)s_leb, scale};
+                                     (lds_ptr<double>)s_leb};
   // the cell relative to the tile (periodic fold); false outside the tile's
   // drift allowance
   auto locate = [&](const int* c3, int* l) {
@@ -772,21 +726,6 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
         R lX0[3], lu0[3], v[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
         if (ok) {
           adjoint_back<DIMS, ORDER, R>(P, ac, l, s0, s, f, lam, p, lX0, lu0, v, v + 3);
-          if constexpr (sizeof(R) == 4) {
-            unsigned b = 0u;
-#pragma unroll
-            for (int c = 0; c < 6; ++c) b = max(b, __float_as_uint((float)v[c]) & 0x7fffffffu);
-            if (b < 0x7f800000u) {
-              big = max(big, b);
-            } else {  // infinite or NaN: the fixed-point sums cannot hold it
-              defer(p);
-              ok = false;
-#pragma unroll
-              for (int c = 0; c < 6; ++c) v[c] = R(0);
-            }
-          }
-        }
-        if (ok) {
 #pragma unroll
           for (int d = 0; d < DIMS; ++d) lam.off[d][p] = lX0[d];
 #pragma unroll
@@ -852,15 +791,8 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
       if (!more) break;
     }
   }
-  if constexpr (PHASE == PDA_BACK && sizeof(R) == 4) {
-    for (int d = 32; d > 0; d >>= 1) big = max(big, (unsigned)__shfl_xor((int)big, d, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(&s_big, big);
-    __syncthreads();
-    if (threadIdx.x == 0) tile_big[tile] = s_big;
-  }
   if constexpr (!G::has_leb) return;
   __syncthreads();
-  const double inv_scale = 1.0 / scale;
   // lamE, lamB of the region (its halo overlaps the neighbouring regions')
   for (int r = threadIdx.x; r < G::e_vol; r += G::NT) {
     const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
@@ -875,7 +807,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
       const int ix = sx[isb ? (e != 0) : (e == 0)];
       const int iy = sy[isb ? (e != 1) : (e == 1)];
       const int iz = sz[isb ? (e != 2) : (e == 2)];
-      const double v = G::has_leb ? ac.sum(s_leb[c * G::e_vol + r], inv_scale) : 0.0;
+      const double v = G::has_leb ? s_leb[c * G::e_vol + r] : 0.0;
       if (v != 0.0 && ix >= 0 && iy >= 0 && iz >= 0) atomicAdd(&(isb ? L.B : L.E)[e][ix + iy + iz], (R)v);
     }
   }
@@ -921,15 +853,13 @@ int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
   if (ctx->sorted_np == p->np && ctx->sorted_ws == ws) {
     const int* starts = (const int*)((char*)ws + Lw.starts);
     int* deferred = (int*)((char*)ws + Lw.tmp_cell);
-    // (the sort's and the re-binned pass's scratch, free here)
-    R* lam_eb = (R*)((char*)ws + Lw.tmp_real);
-    unsigned* tile_big = (unsigned*)((char*)ws + Lw.rb_tv);
+    R* lam_eb = (R*)((char*)ws + Lw.tmp_real);  // (the sort's scratch, free here)
     k_adj_reset<<<dim3(1), dim3(1), 0, s>>>(flg);
     auto phase = [&](auto ph) {
       constexpr int PH = decltype(ph)::value;
       using G = AdjGeo<DIMS, ORDER, R, PH>;
       k_pda_tile<DIMS, ORDER, R, PH><<<dim3(8 * P.per_xcd * G::S), dim3(G::NT), 0, s>>>(
-          P, pa, F, L, la, lam_eb, tile_big, (long)p->np, starts, deferred, flg);
+          P, pa, F, L, la, lam_eb, (long)p->np, starts, deferred, flg);
     };
     if constexpr (DIMS == 2) {
       phase(std::integral_constant<int, PDA_ALL>{});
