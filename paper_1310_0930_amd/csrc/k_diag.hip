@@ -271,7 +271,10 @@ __global__ void __launch_bounds__(256) k_diag_fields(DiagParams P, const R* E0, 
                               double* __restrict__ part) {
   __shared__ double red[NPART][4];
   double v[NPART] = {0, 0, 0, 0, 0, 0};
-  for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.ncell; idx += gridDim.x * blockDim.x) {
+  // (unsigned: the last stride may pass 2^31)
+  for (uint32_t cell = blockIdx.x * blockDim.x + threadIdx.x; cell < (uint32_t)P.ncell;
+       cell += gridDim.x * blockDim.x) {
+    const int idx = (int)cell;
     const uint32_t rest = P.dn0.div((uint32_t)idx);
     int L[3];
     L[0] = idx - (int)rest * P.n[0];
