@@ -112,6 +112,10 @@ class Runner:
                 P.pic_field_advance_adjoint(s.ctx, lf, ws, s.stream)
                 P.pic_push_deposit_adjoint(s.ctx, parts, fields, lf, lp, ws, s.stream)
             del states
+        if len(starts) == 1 and self.steps > 1:
+            # back to the final state, where the forward left the simulation
+            # (with several segments it ends inside the first one)
+            self._step()
         g_a0 = (lamE * self.E_unit).sum(dtype=torch.float64) + (lamB * self.B_unit).sum(dtype=torch.float64)
         g_u0 = torch.zeros_like(lamU)
         g_u0[:, self.perm] = lamU[:, : s.np]
