@@ -189,19 +189,47 @@ __device__ __forceinline__ int cell_residue(const SortParams& S, int lc) {
   return (lx + S.rs1 * ly + S.rs2 * lz) % RES;
 }
 
-// Workgroup 0: exclusive scan of the tile counts (nb of them, the dead bin
-// last) into the scatter's cursors (in place) and the push's tile starts
-// (starts[t] = first particle of tile t, starts[nb - 1] = first absorbed
-// particle, starts[nb] = total), SCAN_PER counts per thread and pass.
-// Workgroup 1: a tile's cells by bank residue, order[0 .. ncells) = cells
+// Exclusive scan of the tile counts (nb of them, the dead bin last) into the
+// scatter's cursors (in place) and the push's tile starts (starts[t] = first
+// particle of tile t, starts[nb - 1] = first absorbed particle, starts[nb] =
+// total): SCAN_CHUNK counts per workgroup, SCAN_PER per thread.  The last
+// workgroup lists a tile's cells by bank residue, order[0 .. ncells) = cells
 // sorted by (residue, cell), order[TILE_CELLS_MAX + r] = first entry of
-// residue r (r <= RES).  (Six launches of 2 to 9 us each before.)
-constexpr int SCAN_NT = 1024, SCAN_PER = 8;
+// residue r (r <= RES).  (Six launches of 2 to 9 us each before.)  Meshes of
+// more tiles than one chunk take a launch more for the chunks' sums (bsum);
+// one workgroup going through 10 us per chunk had cost 0.3 ms at 512^3.
+constexpr int SCAN_NT = 1024, SCAN_PER = 8, SCAN_CHUNK = SCAN_NT * SCAN_PER;
+
+// Sum over the workgroup, to every thread (sh: a value per wavefront).
+__device__ __forceinline__ int scan_block_sum(int v, int* sh) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int t = 0;
+#pragma unroll
+  for (int q = 0; q < SCAN_NT / 64; ++q) t += sh[q];
+  __syncthreads();
+  return t;
+}
+
+__global__ void __launch_bounds__(SCAN_NT) k_sort_sums(const int* __restrict__ counts, int nb,
+                                                       int* __restrict__ bsum) {
+  __shared__ int sh[SCAN_NT / 64];
+  const int i0 = (int)(blockIdx.x * SCAN_CHUNK + threadIdx.x);
+  int v = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_PER; ++k) v += i0 + k * SCAN_NT < nb ? counts[i0 + k * SCAN_NT] : 0;
+  v = scan_block_sum(v, sh);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = v;
+}
+
 __global__ void __launch_bounds__(SCAN_NT) k_sort_scan(SortParams S, int* __restrict__ counts, int nb,
+                                                       const int* __restrict__ bsum,
                                                        int* __restrict__ starts,
                                                        int* __restrict__ order) {
   __shared__ int sh[SCAN_NT];
-  if (blockIdx.x == 1) {
+  if (blockIdx.x == gridDim.x - 1) {
     __shared__ int cnt[RES];
     const int ncells = S.T[0] * S.T[1] * S.T[2];
     const int lc = threadIdx.x;
@@ -227,42 +255,39 @@ __global__ void __launch_bounds__(SCAN_NT) k_sort_scan(SortParams S, int* __rest
     }
     return;
   }
+  int before = 0;  // particles of the chunks before this one
+  if (blockIdx.x > 0) {
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += SCAN_NT) before += bsum[b];
+    before = scan_block_sum(before, sh);
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int carry = 0;
-  for (int base = 0; base < nb; base += SCAN_NT * SCAN_PER) {
-    const int i0 = base + (int)threadIdx.x * SCAN_PER;
-    int v[SCAN_PER], sum = 0;
+  const int i0 = (int)blockIdx.x * SCAN_CHUNK + (int)threadIdx.x * SCAN_PER;
+  int v[SCAN_PER], sum = 0;
 #pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-      v[k] = i0 + k < nb ? counts[i0 + k] : 0;
-      sum += v[k];
-    }
-    int incl = sum;  // over the wavefront's threads
+  for (int k = 0; k < SCAN_PER; ++k) {
+    v[k] = i0 + k < nb ? counts[i0 + k] : 0;
+    sum += v[k];
+  }
+  int incl = sum;  // over the wavefront's threads
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int x = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += x;
-    }
-    if (lane == 63) sh[wave] = incl;
-    __syncthreads();
-    int before = carry, total = 0;  // earlier wavefronts, and all of them
+  for (int d = 1; d < 64; d <<= 1) {
+    const int x = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += x;
+  }
+  if (lane == 63) sh[wave] = incl;
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < SCAN_NT / 64; ++q) {
-      if (q < wave) before += sh[q];
-      total += sh[q];
-    }
-    int ex = before + incl - sum;
+  for (int q = 0; q < SCAN_NT / 64; ++q)  // earlier wavefronts
+    if (q < wave) before += sh[q];
+  int ex = before + incl - sum;
 #pragma unroll
-    for (int k = 0; k < SCAN_PER; ++k) {
-      if (i0 + k < nb) {
-        starts[i0 + k] = ex;
-        counts[i0 + k] = ex;
-        if (i0 + k == nb - 1) starts[nb] = ex + v[k];
-      }
-      ex += v[k];
+  for (int k = 0; k < SCAN_PER; ++k) {
+    if (i0 + k < nb) {
+      starts[i0 + k] = ex;
+      counts[i0 + k] = ex;
+      if (i0 + k == nb - 1) starts[nb] = ex + v[k];
     }
-    carry += total;
-    __syncthreads();
+    ex += v[k];
   }
 }
 
@@ -739,7 +764,10 @@ static int launch_sort_t(const pic_ctx* ctx, const pic_particles* p, void* ws, h
   const long cchunk = (long)COUNT_NT * COUNT_PER, schunk = (long)SCATTER_NT * SCATTER_PER;
   k_sort_count<<<dim3((unsigned)((np + cchunk - 1) / cchunk)), dim3(COUNT_NT), 0, s>>>(
       S, p->cell, np, ncell, counts, flg);
-  k_sort_scan<<<dim3(2), dim3(SCAN_NT), 0, s>>>(S, counts, nb, starts, order);
+  const unsigned chunks = (unsigned)((nb + SCAN_CHUNK - 1) / SCAN_CHUNK);
+  int* bsum = (int*)(w + L.bstart);  // (the re-binned pass's, free here)
+  if (chunks > 1) k_sort_sums<<<dim3(chunks), dim3(SCAN_NT), 0, s>>>(counts, nb, bsum);
+  k_sort_scan<<<dim3(chunks + 1), dim3(SCAN_NT), 0, s>>>(S, counts, nb, bsum, starts, order);
   SortArrays<R> A;
   A.cell = p->cell;
   R* tr = (R*)(w + L.tmp_real);

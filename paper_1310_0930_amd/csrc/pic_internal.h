@@ -210,7 +210,7 @@ struct WsLayout {
   size_t flags;      // DevFlags
   size_t starts;     // int32[ntiles + 2]   tile starts (entry ntiles = dead bin start, then np)
   size_t counts;     // int32[nbins]        bin counts / scatter cursors
-  size_t bstart;     // int32[nbins + 1]    bin starts
+  size_t bstart;     // int32[nbins + 1]    re-binned pass: list positions; sort: sums of the scan's chunks
   size_t rb_tv;      // int32[ntiles]       re-binned pass: slot of each destination tile
   size_t rb_nl;      // int32[ntiles]       re-binned pass: destination tiles
   size_t keys;       // int32[np]           re-binned pass: ranks of the deferred particles
