@@ -35,7 +35,7 @@ namespace pic {
 // each time.  Instead the main loop deposits only single-segment paths, and
 // crossing paths go to a queue (structure of arrays in LDS) shared by the
 // workgroup's wavefronts, which is split and deposited after the tile's
-// batches in whole 64-lane rounds, each lane splitting its own path (with
+// batches in whole 64-lane rounds, one or four lanes per path (with
 // per-wavefront queues a wavefront collected only about nine paths per tile
 // and drained them in a mostly idle round).  Paths beyond the queue's
 // capacity are split in place.  Used where the queue still fits next to the
@@ -358,19 +358,30 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
     const int lane = threadIdx.x & 63;
     // The crossing queue is drained after the barrier that ends the tile's
     // batches, once the next tile's fields (loaded meanwhile) are in LDS, in
-    // rounds dealt round-robin to the wavefronts.  2D: 64 paths a round, every
-    // lane splits its path and deposits all of its segments.  3D: 16 paths a
-    // round, four lanes per path, each deposits one of its (at most four)
-    // segments; the lanes of a path are 16 apart, because the LDS serves
-    // eight-byte atomics 16 lanes at a time and a path's lanes mostly add to
-    // the same samples.  A warm 3D tile's 140 paths are then one round of
-    // nine wavefronts that lasts a segment instead of one of three that lasts
-    // the longest path (128^3 FP32, 20 steps: 20.96 -> 20.63 ms; the 512x256
-    // laser, whose tiles queue hundreds of paths, 2.51 -> 2.57 ms).  (Early
-    // finishers draining while others still push was slower: the adds go to
-    // unsorted cells and slow the batches they run beside.)
-    constexpr int QL = DIMS == 3 ? 4 : 1;  // lanes per path
-    auto drain = [&](int total) {
+    // rounds dealt round-robin to the wavefronts: 64 paths a round, every lane
+    // splits its path and deposits all of its segments, or 16 paths a round,
+    // four lanes per path, each deposits one of its (at most four) segments.
+    // Four lanes of a path are 16 apart, because the LDS serves eight-byte
+    // atomics 16 lanes at a time and a path's lanes mostly add to the same
+    // samples.  A warm 3D tile's 140 paths are then one round of nine wavefronts
+    // that lasts a segment instead of one of three that lasts the longest path,
+    // but every lane splits its path again: they take less time where a segment
+    // is much work beside the split.  72x64x64, 8 and 16 per cell, us a push with
+    // four lanes and with one: FP32 quadratic 160/257 and 162/257, cubic 331/560
+    // and 335/564, quartic 595/1024 and 613/1028, FP64 quartic 1273/1967 and
+    // 1287/2019; but FP32 linear 86/125 and 87/121, FP64 linear 122/191 and
+    // 119/182, and FP64 quadratic and cubic alike, where one lane saves 5 % of the
+    // VALU instructions (128^3 FP64 quadratic: tile kernel 1183 and 1173 us).  In
+    // 2D, where tiles queue hundreds of paths, one lane is the faster (512x256
+    // laser 2.57 and 2.51 ms), and in FP32 quadratic also where a 3D tile queues
+    // more than one such round (64^3, u_th 1: 385 and 380 us; with cubic and
+    // quartic shapes the second form costs registers and 1 %).  (Early finishers draining while others still push
+    // was slower: the adds go to unsorted cells and slow the batches they run
+    // beside.)
+    constexpr int QL =
+        DIMS == 3 && (sizeof(R) == 4 ? ORDER >= 2 : ORDER == 4) ? 4 : 1;  // lanes per path
+    auto drain_by = [&](int total, auto lanes) {
+      constexpr int QL = decltype(lanes)::value;
       for (int r0 = (int)(threadIdx.x >> 6) * (64 / QL); r0 < total; r0 += G::NT / QL) {
         const int r = r0 + lane % (64 / QL);
         if (r < total) {
@@ -397,6 +408,12 @@ __global__ void __launch_bounds__((Geo<DIMS, ORDER, R>::NT)) k_push_tile(
             deposit_one_lds<DIMS, ORDER, R>(s_j, pb, jf, a0, shq, a1, qr, fr, lane / (64 / QL));
         }
       }
+    };
+    auto drain = [&](int total) {
+      if (QL > 1 && ORDER == 2 && total > G::NT / QL)
+        drain_by(total, std::integral_constant<int, 1>{});
+      else
+        drain_by(total, std::integral_constant<int, QL>{});
     };
     // Wavefronts take batches of 64 consecutive particles from a counter in
     // LDS, so that the wavefronts the SIMD arbiter serves first take more
