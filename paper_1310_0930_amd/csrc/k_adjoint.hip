@@ -118,10 +118,14 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   using B = Geo<DIMS, ORDER, R>;
   using Rc = typename B::Rc;
   static constexpr bool has_lj = PHASE != PDA_GATHER, has_leb = PHASE != PDA_BACK;
-  static constexpr size_t bytes(int tz) {
+  // padded: the field region's rows and planes are the push's, which the sort
+  // spreads the lanes by; else they are dense
+  static constexpr size_t bytes(int tz, bool padded) {
+    const int nz = DIMS == 3 ? tz + 2 * B::AZ + Rc::g_hi - Rc::g_lo : 1;
+    const int mz = DIMS == 3 ? tz + 2 * B::AZ + Rc::d_hi - Rc::d_lo : 1;
     return (sizeof(R) * 6 + (has_leb ? sizeof(double) * 6 : 0)) *
-               (size_t)(B::ex * B::ex * (tz + 2 * B::AZ + Rc::g_hi - Rc::g_lo)) +
-           (has_lj ? sizeof(R) * 3 * (size_t)(B::jx * B::jx * (tz + 2 * B::AZ + Rc::d_hi - Rc::d_lo)) : 0);
+               (size_t)((padded ? B::ep : B::ex * B::ex) * nz) +
+           (has_lj ? sizeof(R) * 3 * (size_t)(B::jx * B::jx * mz) : 0);
   }
   static constexpr size_t LDS_MAX = 160 * 1024;
   // the gather's transpose needs few registers: 16 wavefronts in FP32
@@ -134,18 +138,25 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   // 128 indices per wavefront
   static constexpr int QCAP = 128;
   static constexpr size_t queue_bytes = sizeof(int) * QCAP * (NT / 64);
-  static constexpr int pick() {
+  static constexpr int pick(bool padded) {
     if (DIMS == 2) return 1;
     for (int s = 1; s <= B::TZ; s *= 2)
-      if (B::TZ % s == 0 && bytes(B::TZ / s) + (s > 1 ? queue_bytes : 0) <= LDS_MAX) return s;
+      if (B::TZ % s == 0 && bytes(B::TZ / s, padded) + (s > 1 ? queue_bytes : 0) <= LDS_MAX) return s;
     return 0;
   }
-  static constexpr int S = pick();
+  static constexpr int S = pick(false);
   static_assert(S > 0, "one-cell slabs fit");
+  // workgroups whose regions share a CU's LDS
+  static constexpr size_t per_cu(bool padded) {
+    return LDS_MAX / (bytes(B::TZ / S, padded) + (S > 1 ? queue_bytes : 0) + 64);
+  }
+  // padded where that costs no slab and no workgroup on a CU (2D linear FP32,
+  // 512x256 at 16 per cell: 87 -> 81 us)
+  static constexpr bool pad = pick(true) == S && per_cu(true) == per_cu(false);
   static constexpr int TZ = B::TZ / S;
   static constexpr int ez = DIMS == 3 ? TZ + 2 * B::AZ + Rc::g_hi - Rc::g_lo : 1;
-  static constexpr int es = B::ex, ep = B::ex * B::ex;
-  static constexpr int e_vol = ep * ez, e_cnt = e_vol;
+  static constexpr int es = pad ? B::es : B::ex, ep = pad ? B::ep : B::ex * B::ex;
+  static constexpr int e_vol = ep * ez, e_cnt = B::ex * B::ex * ez;
   static constexpr int jz = DIMS == 3 ? TZ + 2 * B::AZ + Rc::d_hi - Rc::d_lo : 1;
   static constexpr int j_vol = B::jx * B::jx * jz;
 };
@@ -644,15 +655,16 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
   const int open2 = DIMS == 3 && P.bc[2] == PIC_BC_OPEN;
   const int str1 = P.n[0], str2 = P.n[0] * P.n[1];
   {
-    constexpr int NR = (G::e_vol + G::NT - 1) / G::NT;
+    constexpr int NR = (G::e_cnt + G::NT - 1) / G::NT;
     R stage[NR][6];
     stage_load<DIMS, ORDER, R, NR, G>(P, F, org, stage, (int)threadIdx.x, G::NT);
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int r = threadIdx.x + k * G::NT;
-      if (r < G::e_vol) {
+      if (r < G::e_cnt) {
+        const int e = r / (G::ex * G::ex) * G::ep + (r / G::ex) % G::ex * G::es + r % G::ex;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) s_eb[c * G::e_vol + r] = stage[k][c];
+        for (int c = 0; c < 6; ++c) s_eb[c * G::e_vol + e] = stage[k][c];
       }
     }
   }
@@ -794,8 +806,9 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
   if constexpr (!G::has_leb) return;
   __syncthreads();
   // lamE, lamB of the region (its halo overlaps the neighbouring regions')
-  for (int r = threadIdx.x; r < G::e_vol; r += G::NT) {
+  for (int r = threadIdx.x; r < G::e_cnt; r += G::NT) {
     const int lx = r % G::ex, ly = (r / G::ex) % G::ex, lz = r / (G::ex * G::ex);
+    const int t = lz * G::ep + ly * G::es + lx;
     int sx[2], sy[2], sz[2] = {0, 0};
     axis_slots(org[0] + G::e_lo + lx, P.n[0], open0, 1, sx);
     axis_slots(org[1] + G::e_lo + ly, P.n[1], open1, str1, sy);
@@ -807,7 +820,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
       const int ix = sx[isb ? (e != 0) : (e == 0)];
       const int iy = sy[isb ? (e != 1) : (e == 1)];
       const int iz = sz[isb ? (e != 2) : (e == 2)];
-      const double v = G::has_leb ? s_leb[c * G::e_vol + r] : 0.0;
+      const double v = G::has_leb ? s_leb[c * G::e_vol + t] : 0.0;
       if (v != 0.0 && ix >= 0 && iy >= 0 && iz >= 0) atomicAdd(&(isb ? L.B : L.E)[e][ix + iy + iz], (R)v);
     }
   }

@@ -58,13 +58,17 @@ struct Geo {
   // FP32 sorts by (1, 14, 196) and takes the current rows at (15, 2, 252) =
   // -(1, 14, 4) modulo 16 (15 x + 2 y names each of the 15 x 15 samples of a
   // plane once), linear FP32 by (1, 12, 144) with (15, 4, 240); the others pad
-  // both regions to like rows and planes.  (Replaying the sort's lane order,
+  // both regions to like rows and planes.  In 2D cubic the field rows stay at
+  // 24 and the current rows are 40 = 24 modulo 16: with 28 in both, the step
+  // adjoint, which sums lamE and lamB on the sort's lanes, met 1.6 times the
+  // conflicts (512x256 FP32, 16 per cell: 236 -> 195 us; push 67.9 us either
+  // way).  (Replaying the sort's lane order,
   // the cubic FP32 deposit takes 1.6 LDS passes per add instead of 3.4, the
   // linear one 1.6 instead of 3.0; the quartic regions are padded because
   // (1, 15, 225) leaves some residues with 1 cell of the tile and others with
   // 14: 1.7 passes instead of 2.5.)
   static constexpr bool sgl = sizeof(R) == 4;
-  static constexpr int es = DIMS == 2    ? (ORDER == 1 ? 24 : ORDER == 2 ? ex : 28)
+  static constexpr int es = DIMS == 2    ? (ORDER == 1 ? 24 : ORDER <= 3 ? ex : 28)
                             : ORDER == 1 ? (sgl ? ex : 13)
                             : ORDER == 3 ? (sgl ? ex : 15)
                                          : ex;
@@ -75,7 +79,7 @@ struct Geo {
                                          : es * ex;
   static constexpr bool skew = DIMS == 3 && sgl && (ORDER & 1);
   static constexpr int ja = skew ? 15 : 1;
-  static constexpr int jb = skew ? (ORDER == 1 ? 4 : 2) : DIMS == 2 ? es : jx;
+  static constexpr int jb = skew ? (ORDER == 1 ? 4 : 2) : DIMS == 2 ? (ORDER == 3 ? 40 : es) : jx;
   static constexpr int jc = DIMS == 2    ? jb * jx
                             : ORDER == 1 ? (sgl ? 240 : 181)
                             : ORDER == 3 ? (sgl ? 252 : 227)
