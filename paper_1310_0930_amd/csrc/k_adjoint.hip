@@ -205,7 +205,9 @@ struct AdjLds {
 // derivatives per axis are w and dw, from its first stencil node: every node's
 // adjoint receives w lam, and lX the derivative of the interpolated value times
 // lam.  The sums over the stencil are nested (x, then y, then z), two products
-// per sample.
+// per sample.  A plane's samples are read before anything is added: the LDS
+// answers in order, and a read behind an add waits for it (96x80x64 FP64
+// quadratic: 1191 -> 1134 us).
 template <int DIMS, int ORDER, typename R, class Acc>
 __device__ __forceinline__ void gather_vjp_comp(const Acc& ac, int comp, const int* first,
                                                 const R (*w)[ORDER + 1], const R (*dw)[ORDER + 1],
@@ -218,13 +220,18 @@ __device__ __forceinline__ void gather_vjp_comp(const Acc& ac, int comp, const i
   for (int k = 0; k < MZ; ++k) {
     R s = R(0), dy = R(0), dx = R(0);
     const R lz = DIMS == 3 ? w[2][k] * lam : lam;
+    R fp[M][M];
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+      for (int i = 0; i < M; ++i) fp[j][i] = ac.at(r, i, j, k);
 #pragma unroll
     for (int j = 0; j < M; ++j) {
       R sx = R(0), dxx = R(0);
       const R lyz = w[1][j] * lz;
 #pragma unroll
       for (int i = 0; i < M; ++i) {
-        const R f = ac.at(r, i, j, k);
+        const R f = fp[j][i];
         sx += w[0][i] * f;
         dxx += dw[0][i] * f;
         ac.add(r, i, j, k, w[0][i] * lyz);
