@@ -113,7 +113,7 @@ enum { PDA_ALL = 0, PDA_BACK = 1, PDA_GATHER = 2 };
 // precision, lamE/lamB in double) of a whole 3D tile exceed a CU's LDS.
 // Each slab keeps the tile's drift allowance and stencil reach; x and y are
 // the tile's.
-template <int DIMS, int ORDER, typename R, int PHASE>
+template <int DIMS, int ORDER, typename R, int PHASE, int NT2>
 struct AdjGeo : Geo<DIMS, ORDER, R> {
   using B = Geo<DIMS, ORDER, R>;
   using Rc = typename B::Rc;
@@ -129,7 +129,7 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
   }
   static constexpr size_t LDS_MAX = 160 * 1024;
   // the gather's transpose needs few registers: 16 wavefronts in FP32
-  static constexpr int NT = PHASE == PDA_GATHER && sizeof(R) == 4 ? 1024 : 512;
+  static constexpr int NT = DIMS == 2 ? NT2 : PHASE == PDA_GATHER && sizeof(R) == 4 ? 1024 : 512;
   // wavefronts per SIMD to keep registers for: up to quadratic order in FP32
   // two workgroups of PDA_BACK share a CU (in 2D, where there are 512 tiles for
   // 256 CUs, the spills cost more: 512x256 quadratic FP32 138 against 129 us)
@@ -638,12 +638,12 @@ __global__ void __launch_bounds__(256) k_push_deposit_adjoint(KParams<R> P, DPar
 // list for the global-memory kernel (entered by PDA_ALL or PDA_BACK, which has
 // one slab); PDA_BACK leaves zeros in `lam_eb` (6 arrays of np) for the ones
 // that moved too far or became non-finite, and PDA_GATHER skips zeros.
-template <int DIMS, int ORDER, typename R, int PHASE>
-__global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE>::NT),
-                                  (AdjGeo<DIMS, ORDER, R, PHASE>::WPE)) k_pda_tile(
+template <int DIMS, int ORDER, typename R, int PHASE, int NT2>
+__global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE, NT2>::NT),
+                                  (AdjGeo<DIMS, ORDER, R, PHASE, NT2>::WPE)) k_pda_tile(
     KParams<R> P, DParts<R> pa, DFields<R> F, DFields<R> L, DParts<R> lam, R* __restrict__ lam_eb,
     long np, const int* __restrict__ starts, int* __restrict__ deferred, DevFlags* flg) {
-  using G = AdjGeo<DIMS, ORDER, R, PHASE>;
+  using G = AdjGeo<DIMS, ORDER, R, PHASE, NT2>;
   constexpr int S = G::S;
   __shared__ R s_eb[6 * G::e_vol];
   __shared__ R s_lj[G::has_lj ? 3 * G::j_vol : 1];
@@ -875,17 +875,30 @@ int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
     int* deferred = (int*)((char*)ws + Lw.tmp_cell);
     R* lam_eb = (R*)((char*)ws + Lw.tmp_real);  // (the sort's scratch, free here)
     k_adj_reset<<<dim3(1), dim3(1), 0, s>>>(flg);
-    auto phase = [&](auto ph) {
-      constexpr int PH = decltype(ph)::value;
-      using G = AdjGeo<DIMS, ORDER, R, PH>;
-      k_pda_tile<DIMS, ORDER, R, PH><<<dim3(8 * P.per_xcd * G::S), dim3(G::NT), 0, s>>>(
+    auto phase = [&](auto ph, auto nt) {
+      constexpr int PH = decltype(ph)::value, NT2 = decltype(nt)::value;
+      using G = AdjGeo<DIMS, ORDER, R, PH, NT2>;
+      k_pda_tile<DIMS, ORDER, R, PH, NT2><<<dim3(8 * P.per_xcd * G::S), dim3(G::NT), 0, s>>>(
           P, pa, F, L, la, lam_eb, (long)p->np, starts, deferred, flg);
     };
+    const std::integral_constant<int, PDA_ALL> all{};
+    const std::integral_constant<int, 512> nt512{};
     if constexpr (DIMS == 2) {
-      phase(std::integral_constant<int, PDA_ALL>{});
+      // 8 wavefronts where every tile has a CU to itself.  Where tiles share
+      // CUs, 4 wavefronts let two of them run side by side; with 8 only forms
+      // of up to 128 registers do (linear FP32), and cubic FP64 takes so many
+      // with 4 that no two fit (us with 8 and with 4 wavefronts: 300x200, 247
+      // tiles, FP32 linear 33/44, quadratic 45/61, cubic 72/92; 1024x1024, 4096
+      // tiles, FP32 linear 277/293, quadratic 568/436, cubic 1000/857, FP64
+      // linear 501/444, cubic 1201/1341).
+      constexpr bool wide = (sizeof(R) == 4 && ORDER == 1) || (sizeof(R) == 8 && ORDER == 3);
+      if (wide || P.ntiles <= ctx->cu_count)
+        phase(all, nt512);
+      else if constexpr (!wide)
+        phase(all, std::integral_constant<int, 256>{});
     } else {
-      phase(std::integral_constant<int, PDA_BACK>{});
-      phase(std::integral_constant<int, PDA_GATHER>{});
+      phase(std::integral_constant<int, PDA_BACK>{}, nt512);
+      phase(std::integral_constant<int, PDA_GATHER>{}, nt512);
     }
     k_push_deposit_adjoint<DIMS, ORDER, R><<<dim3(gblocks), dim3(256), 0, s>>>(
         P, pa, F, L, la, flg, (int)p->np, deferred, starts + P.ntiles);
