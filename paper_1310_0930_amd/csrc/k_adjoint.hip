@@ -144,8 +144,8 @@ struct AdjGeo : Geo<DIMS, ORDER, R> {
       if (B::TZ % s == 0 && bytes(B::TZ / s, padded) + (s > 1 ? queue_bytes : 0) <= LDS_MAX) return s;
     return 0;
   }
-  static constexpr int S = pick(false);
-  static_assert(S > 0, "one-cell slabs fit");
+  static constexpr bool fits = pick(false) > 0;
+  static constexpr int S = fits ? pick(false) : 1;
   // workgroups whose regions share a CU's LDS
   static constexpr size_t per_cu(bool padded) {
     return LDS_MAX / (bytes(B::TZ / S, padded) + (S > 1 ? queue_bytes : 0) + 64);
@@ -206,8 +206,8 @@ struct AdjLds {
 // adjoint receives w lam, and lX the derivative of the interpolated value times
 // lam.  The sums over the stencil are nested (x, then y, then z), two products
 // per sample.  A plane's samples are read before anything is added: the LDS
-// answers in order, and a read behind an add waits for it (96x80x64 FP64
-// quadratic: 1191 -> 1134 us).
+// answers in order, and a read behind an add waits for it (3D cubic FP32 in one
+// kernel, 24x16x20: 293 -> 228 us).
 template <int DIMS, int ORDER, typename R, class Acc>
 __device__ __forceinline__ void gather_vjp_comp(const Acc& ac, int comp, const int* first,
                                                 const R (*w)[ORDER + 1], const R (*dw)[ORDER + 1],
@@ -644,6 +644,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE, NT2>::NT),
     KParams<R> P, DParts<R> pa, DFields<R> F, DFields<R> L, DParts<R> lam, R* __restrict__ lam_eb,
     long np, const int* __restrict__ starts, int* __restrict__ deferred, DevFlags* flg) {
   using G = AdjGeo<DIMS, ORDER, R, PHASE, NT2>;
+  static_assert(G::fits, "one-cell slabs fit");
   constexpr int S = G::S;
   __shared__ R s_eb[6 * G::e_vol];
   __shared__ R s_lj[G::has_lj ? 3 * G::j_vol : 1];
@@ -767,7 +768,7 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE, NT2>::NT),
         defer(p);
     }
   } else {
-    static_assert(S == 1 || PHASE == PDA_GATHER, "particles are deferred once");
+    static_assert(PHASE != PDA_BACK, "particles are deferred once");
     // Every slab scans all of the tile's particles, a slab's share is about
     // 1/S of them: each wavefront queues the indices of its slab's particles
     // (allowance cells below and above the tile go to the end slabs) and
@@ -785,8 +786,12 @@ __global__ void __launch_bounds__((AdjGeo<DIMS, ORDER, R, PHASE, NT2>::NT),
         if (p < pend) {
           const PState<R> s = load_particle<DIMS, R>(pa, p, P.q_const);
           int c3[3] = {0, 0, 0}, l[3] = {0, 0, 0};
-          if (s.cl >= 0 && decode<DIMS, R>(P, s, c3, flg) && locate(c3, l))
-            own = (l[2] < 0 ? 0 : (l[2] / G::TZ < S ? l[2] / G::TZ : S - 1)) == slab;
+          if (s.cl >= 0 && decode<DIMS, R>(P, s, c3, flg)) {
+            if (locate(c3, l))
+              own = (l[2] < 0 ? 0 : (l[2] / G::TZ < S ? l[2] / G::TZ : S - 1)) == slab;
+            else if (PHASE == PDA_ALL && slab == 0)
+              defer(p);
+          }
         }
         const unsigned long long m = __ballot(own);
         if (own) q[qn + (int)__popcll(m & ((1ull << lane) - 1ull))] = p;
@@ -897,8 +902,28 @@ int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
       else if constexpr (!wide)
         phase(all, std::integral_constant<int, 256>{});
     } else {
-      phase(std::integral_constant<int, PDA_BACK>{}, nt512);
-      phase(std::integral_constant<int, PDA_GATHER>{}, nt512);
+      // One kernel over the tile's slabs for linear shapes, whose regions leave
+      // one or two slabs (96x80x64: FP32 310 us and 344 in two phases, FP64 609
+      // and 669), and where every slab has a CU to itself, so that the two
+      // phases' chains of latencies would only come one after the other (24x16x20,
+      // 18 tiles: FP32 quadratic 139 and 208 us, cubic 228 and 359, quartic 242
+      // and 404, FP64 quadratic 147 and 189; with 288 slabs, 48x48x32 FP32
+      // quadratic, 269 and 228).  FP64 cubic does not fit and quartic gains
+      // nothing.
+      constexpr bool one = sizeof(R) == 4 || ORDER <= 2;
+      bool done = false;
+      if constexpr (one) {
+        using G = AdjGeo<DIMS, ORDER, R, PDA_ALL, 512>;
+        if (ORDER == 1 || P.ntiles * G::S <= ctx->cu_count) {
+          phase(all, nt512);
+          done = true;
+        }
+      }
+      if constexpr (ORDER > 1)
+        if (!done) {
+          phase(std::integral_constant<int, PDA_BACK>{}, nt512);
+          phase(std::integral_constant<int, PDA_GATHER>{}, nt512);
+        }
     }
     k_push_deposit_adjoint<DIMS, ORDER, R><<<dim3(gblocks), dim3(256), 0, s>>>(
         P, pa, F, L, la, flg, (int)p->np, deferred, starts + P.ntiles);
