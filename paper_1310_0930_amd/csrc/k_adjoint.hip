@@ -889,15 +889,20 @@ int launch_pda(const pic_ctx* ctx, const pic_particles* p, const pic_fields* f,
     const std::integral_constant<int, PDA_ALL> all{};
     const std::integral_constant<int, 512> nt512{};
     if constexpr (DIMS == 2) {
-      // 8 wavefronts where every tile has a CU to itself.  Where tiles share
-      // CUs, 4 wavefronts let two of them run side by side; with 8 only forms
-      // of up to 128 registers do (linear FP32), and cubic FP64 takes so many
-      // with 4 that no two fit (us with 8 and with 4 wavefronts: 300x200, 247
-      // tiles, FP32 linear 33/44, quadratic 45/61, cubic 72/92; 1024x1024, 4096
-      // tiles, FP32 linear 277/293, quadratic 568/436, cubic 1000/857, FP64
-      // linear 501/444, cubic 1201/1341).
+      // 8 wavefronts where a CU has at most two tiles, 4 where it has more.  Of
+      // the forms with more than 128 registers (all but linear FP32) one
+      // workgroup of 8 or two of 4 are on a CU; a wavefront more per SIMD hides
+      // more of a tile's own latencies, and two tiles side by side hide each
+      // other's staging and flush, which counts once tiles queue for CUs.  Us with
+      // 8 and with 4: 300x200, 247 tiles, FP32 quadratic 45 and 61, cubic 72 and
+      // 92; 512x256, 512 tiles, FP32 quadratic right after a sort 133 and 129, a
+      // laser rollout of 10 steps, whose particles have drifted, 3516 and 3650;
+      // 1024x1024, 4096 tiles, FP32 quadratic 568 and 436, cubic 1000 and 857,
+      // FP64 linear 501 and 444.  Linear FP32 and cubic FP64 (which takes so many
+      // registers with 4 that no two fit) are the faster with 8 at every size
+      // (1024x1024: 277 and 293, 1201 and 1341).
       constexpr bool wide = (sizeof(R) == 4 && ORDER == 1) || (sizeof(R) == 8 && ORDER == 3);
-      if (wide || P.ntiles <= ctx->cu_count)
+      if (wide || P.ntiles <= 2 * ctx->cu_count)
         phase(all, nt512);
       else if constexpr (!wide)
         phase(all, std::integral_constant<int, 256>{});

@@ -1,7 +1,7 @@
 """The step adjoint's LDS forms against global memory, element by element, where
-the launch's rules choose another form: meshes of more tiles than CUs (2D
-workgroups of 4 wavefronts, 3D in two phases from quadratic order on) and of
-fewer, open faces, ragged last tiles, cubic FP64."""
+the launch's rules choose another form: meshes of many tiles per CU (2D
+workgroups of 4 wavefronts; 3D in two phases from quadratic order on) and of
+few, open faces, ragged last tiles, cubic FP64."""
 import pytest
 
 from paper_1310_0930_amd import inputs as I
@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rb", [4, 8])
 @pytest.mark.parametrize("order", [1, 2, 3, 4])
 def test_many_tiles_2d(order, rb):
-    """19 x 17 tiles."""
-    w = I.Workload("adjf2", 2, (300, 261), (0.1, 0.2), order, 3, 0.2, 1, bc=(0, 1), ramp_cells=6.0,
+    """25 x 22 tiles."""
+    w = I.Workload("adjf2", 2, (400, 341), (0.1, 0.2), order, 2, 0.2, 1, bc=(0, 1), ramp_cells=6.0,
                    seed=I.SEED_BASE + 220 + order)
     _tiled_vs_global(w, rb, 51 + order)
 
