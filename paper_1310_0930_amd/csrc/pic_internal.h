@@ -62,18 +62,24 @@ struct Geo {
   // 24 and the current rows are 40 = 24 modulo 16: with 28 in both, the step
   // adjoint, which sums lamE and lamB on the sort's lanes, met 1.6 times the
   // conflicts (512x256 FP32, 16 per cell: 236 -> 195 us; push 67.9 us either
-  // way).  (Replaying the sort's lane order,
-  // the cubic FP32 deposit takes 1.6 LDS passes per add instead of 3.4, the
+  // way).  (A host model of the sort's lane order
+  // gives the cubic FP32 deposit 1.6 LDS passes per add instead of 3.4, the
   // linear one 1.6 instead of 3.0; the quartic regions are padded because
   // (1, 15, 225) leaves some residues with 1 cell of the tile and others with
   // 14: 1.7 passes instead of 2.5.)
+  // Padding takes LDS from the crossing queue.  Push at 72x64x64, us with dense
+  // and with these strides: FP32 cubic 397 and 331 at 8 per cell, 692 and 560 at
+  // 16, quartic 711 and 595, 1204 and 1020, linear alike; FP64 cubic (80 queued
+  // paths for 321) 553 and 510 at 8 per cell, 980 and 971 at 16, but at u_th 0.2
+  // 661 and 695, 1260 and 1255; FP64 linear (383 for 878) alike at u_th 0.05 and
+  // 155 and 164, 239 and 253 at 0.2, so it stays dense.
   static constexpr bool sgl = sizeof(R) == 4;
   static constexpr int es = DIMS == 2    ? (ORDER == 1 ? 24 : ORDER <= 3 ? ex : 28)
-                            : ORDER == 1 ? (sgl ? ex : 13)
+                            : ORDER == 1 ? ex
                             : ORDER == 3 ? (sgl ? ex : 15)
                                          : ex;
   static constexpr int ep = DIMS == 2    ? es * ex
-                            : ORDER == 1 ? (sgl ? es * ex : 165)
+                            : ORDER == 1 ? es * ex
                             : ORDER == 3 ? (sgl ? es * ex : 211)
                             : ORDER == 4 ? (sgl ? 248 : es * ex)
                                          : es * ex;
@@ -81,7 +87,7 @@ struct Geo {
   static constexpr int ja = skew ? 15 : 1;
   static constexpr int jb = skew ? (ORDER == 1 ? 4 : 2) : DIMS == 2 ? (ORDER == 3 ? 40 : es) : jx;
   static constexpr int jc = DIMS == 2    ? jb * jx
-                            : ORDER == 1 ? (sgl ? 240 : 181)
+                            : ORDER == 1 ? (sgl ? 240 : jb * jx)
                             : ORDER == 3 ? (sgl ? 252 : 227)
                             : ORDER == 4 ? (sgl ? 248 : jb * jx)
                                          : jb * jx;
