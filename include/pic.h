@@ -296,9 +296,9 @@ int pic_field_advance_adjoint(pic_ctx* ctx, pic_fields* lam, void* ws, void* str
  * Absorbed particles (cell = -1) are skipped.  When the context's last
  * pic_sort was of state_n->np particles in this `ws`, particles inside the
  * drift allowance of the tile whose bin range holds them are done out of
- * LDS, per tile in 2D and per z slab of a tile in 3D (the rest, and every
- * particle of the cubic FP64 form, in global memory); the result does not
- * depend on that beyond the order of floating-point atomic additions. */
+ * LDS, per tile or, in 3D, per z slab of one (the rest in global memory); the
+ * result does not depend on that beyond the order of floating-point atomic
+ * additions. */
 int pic_push_deposit_adjoint(pic_ctx* ctx, const pic_particles* state_n, const pic_fields* EB_n,
                              pic_fields* lam_f, pic_particles* lam_p, void* ws, void* stream);
 

@@ -174,8 +174,8 @@ __device__ __forceinline__ void mur_faces(R* __restrict__ E, int idx, int sa, in
 // face samples used to be saved to memory and updated by 2 to 12 small
 // launches, and only grids periodic along every axis took columns:
 // 250x131x121, open y and z, FP32: the whole advance 167 -> 95 us, 5.0 TB/s
-// of the 30 reals per cell that the three in-place passes move, about what a
-// large copy reaches).
+// of the 30 reals per cell that the three in-place passes move, where a large
+// copy reaches 4.7: some of what one pass leaves the next still finds in cache).
 template <typename R, int DIMS, int KC, bool OPEN, bool RAGGED>
 __global__ void __launch_bounds__(256) k_advance_e(
     FdParams P, R* __restrict__ E0, R* __restrict__ E1, R* __restrict__ E2,

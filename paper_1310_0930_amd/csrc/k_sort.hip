@@ -356,8 +356,8 @@ __device__ __forceinline__ int placement_key(const SortParams& S, int t, int cl,
 // workgroup takes SCATTER_PER particles per thread (chunks spread as above),
 // ranks them per tile in LDS and moves each tile's cursor once.
 // Bound by the scattered stores of ten arrays, in runs of a tile's share (FP32,
-// one MI355X: 16.8M warm particles 335 -> 270 us, 2.9M behind a moving window
-// 144 -> 41 us; with the count, 77 -> 41 and 116 -> 19 us).
+// one MI355X: 16.8M warm particles 297 -> 224 us, 2.9M behind a moving window
+// 144 -> 41 us; the count 62 -> 38 and 116 -> 19 us).
 constexpr int SCATTER_NT = 256, SCATTER_PER = 4;
 template <typename R>
 __global__ void __launch_bounds__(SCATTER_NT) k_sort_scatter(SortArrays<R> A, SortParams S, long np,

@@ -291,10 +291,10 @@ def test_tiled_step_adjoint_equals_global_memory_adjoint(dims, rb, order, bc):
     """The step adjoint runs out of LDS when the context holds tile bins for
     the particles (same count, same workspace), else one thread per particle
     in global memory.  In 3D a tile is cut into z slabs (one per workgroup)
-    where its regions exceed a CU's LDS: 2 slabs for quadratic FP32 and
-    linear FP64, 4 for cubic FP32 and quadratic FP64, one-cell slabs for
-    quartic FP32 (linear FP32 and quartic FP64 take whole tiles); the 3D
-    grid here has a ragged last tile along z and an open y face, or open y
+    where its regions exceed a CU's LDS, in one kernel (linear shapes, and
+    few tiles as here: 2 slabs for quadratic FP32 and linear FP64, 4 for cubic
+    FP32 and quadratic FP64, one-cell slabs for quartic FP32) or in two phases
+    (FP64 from cubic on); the 3D grid here has a ragged last tile along z and an open y face, or open y
     and z faces (slabs next to the open z face).  Both paths
     must give the same lamX, lamU, lamE, lamB, also for particles in an
     order other than the sort's."""
@@ -311,7 +311,7 @@ def test_tiled_step_adjoint_equals_global_memory_adjoint(dims, rb, order, bc):
 @pytest.mark.parametrize("rb,order", [(8, 2), (4, 2), (4, 3)])
 def test_tiled_step_adjoint_equals_global_memory_adjoint_at_64_cubed(rb, order):
     """The same at the bench plasma's density and temperature on a 64^3 grid
-    (8 ppc, 2.1M particles, 512 tiles, 2 or 4 slabs each), sorted order."""
+    (8 ppc, 2.1M particles, 512 tiles), sorted order."""
     w = I.Workload("adjt64", 3, (64, 64, 64), (0.2, 0.2, 0.2), order, 8, 0.05, 1,
                    seed=I.SEED_BASE + 140 + order)
     _tiled_vs_global(w, rb, 41 + order, shuffled_too=False)

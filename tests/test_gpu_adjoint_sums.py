@@ -1,7 +1,6 @@
-"""The fixed-point sums of the 3D FP32 step adjoint (lamE, lamB of a tile)
-against the global-memory path, where their scale can go wrong: tiles of more
-particles than the scale's headroom starts with, adjoints near both ends of the
-FP32 range, and adjoints that are infinite or NaN."""
+"""The sums of the 3D FP32 step adjoint (lamE, lamB of a tile) against the
+global-memory path: full tiles, adjoints near both ends of the FP32 range, and
+adjoints that are infinite or NaN."""
 import numpy as np
 import pytest
 

@@ -1,5 +1,5 @@
-"""The tile pass of the charge density, in fixed point (particles of one charge,
-order 2 on, from 1.5 per cell) and in double, against the global-memory pass."""
+"""The tile pass of the charge density against the global-memory pass, from one
+particle per cell to all of them on one node."""
 import numpy as np
 import pytest
 

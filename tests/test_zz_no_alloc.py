@@ -1,7 +1,7 @@
 """The no-allocation field advance (pic_field_advance_static) through the C
 ABI: the same result as pic_field_advance with a workspace, on two calls in a
-row (the second on a smaller grid), with open faces so that its static
-scratch (the saved E planes next to open faces) is used."""
+row (the second on a smaller grid), with open faces, whose updates need the E
+samples next to them before and after the step."""
 import ctypes as C
 
 import numpy as np
